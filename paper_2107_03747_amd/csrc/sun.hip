@@ -480,29 +480,51 @@ __device__ __forceinline__ void sun_link_update(const SunStageArgs &a, const Cfg
     store_blk<N, R>(Wout, c.stride, MU, gr, site, mm_nn<N, R>(e, U, gr));
 }
 
-// work-group = one tile of 64 sites; wave w updates direction w for the
-// tile's sites, G = 64 / L at a time (lane = g L + l)
+// Site groups of the stage launches.  A wave holds G = 64 / L sites; the sites
+// of a configuration are cut into groups of G, and every group is a work-group
+// of its own (wave w updates direction w).  ceil(64 / G) work-groups are
+// launched per 64-site tile, enough for every group of the configuration; the
+// few past its end return.  One group per work-group, not a loop over a tile's
+// groups: a 3x3x15x15 SU(5) box is 169 work-groups of one group instead of 32
+// of six in a row (a 16-step flow 7.2 -> 1.8 ms; 4x4x20x20 boxes of 102k sites
+// -19%), and no group is cut at a tile's end.  The launch order gives each XCD
+// one contiguous range of groups.
+template <int G>
+struct SiteGroups {
+    static constexpr int P = (kTile + G - 1) / G;   // work-groups per tile
+};
+
+// site of lane 0 of the group that work-group b takes (-1: none) and its configuration
+template <int G>
+__device__ __forceinline__ int group_first(const SunStageArgs &a, int &ci) {
+    constexpr int P = SiteGroups<G>::P;
+    const int nb = a.n_tiles * P;
+    const int b = remap_block(blockIdx.x, nb, 1);
+    if (b >= nb) return -1;
+    const int tile = b / P;
+    ci = find_cfg(a.tile_start, a.n_act, tile);
+    const int first = (b - a.tile_start[ci] * P) * G;
+    return first < a.cfgs[ci].V ? first : -1;
+}
+
 template <int N, int R>
 __global__ __launch_bounds__(256) void sun_stage_kernel(SunStageArgs a) {
-    const int tile = blockIdx.x;
-    if (tile >= a.n_tiles) return;
-    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ci = find_cfg(a.tile_start, a.n_act, tile);
-    const CfgDesc &c = a.cfgs[ci];   // in global memory: the twist entries are read with run-time indices
     constexpr int L = N / R, G = 64 / L;
+    int ci = 0;
+    const int first = group_first<G>(a, ci);
+    if (first < 0) return;
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const CfgDesc &c = a.cfgs[ci];   // in global memory: the twist entries are read with run-time indices
     const int lane = threadIdx.x & 63;
     const int g = lane / L;
     const Grp gr{g * L, lane - g * L};
-    const int first = (tile - a.tile_start[ci]) * kTile;
-    for (int s0 = 0; s0 < kTile; s0 += G) {
-        const int site = first + s0 + g;
-        if (g >= G || s0 + g >= kTile || site >= c.V) continue;
-        switch (mu) {
-            case 0: sun_link_update<N, R, 0>(a, c, site, gr); break;
-            case 1: sun_link_update<N, R, 1>(a, c, site, gr); break;
-            case 2: sun_link_update<N, R, 2>(a, c, site, gr); break;
-            default: sun_link_update<N, R, 3>(a, c, site, gr); break;
-        }
+    const int site = first + g;
+    if (g >= G || site >= c.V) return;
+    switch (mu) {
+        case 0: sun_link_update<N, R, 0>(a, c, site, gr); break;
+        case 1: sun_link_update<N, R, 1>(a, c, site, gr); break;
+        case 2: sun_link_update<N, R, 2>(a, c, site, gr); break;
+        default: sun_link_update<N, R, 3>(a, c, site, gr); break;
     }
 }
 
@@ -608,17 +630,41 @@ __device__ __forceinline__ double wave_sum_d(double v) {
     return v;
 }
 
-// work-group = one tile of WPB waves; wave w measures the tile's sites
-// SPW w .. SPW w + SPW - 1, G at a time (G = 64 / (N/R) sites fill a wave, so
-// one wave per tile when a lane holds a whole link, two when it holds half);
-// the per-tile sums go to partials[tile][0], slots 1, 2 are zero (the layout
-// of the SU(3) measurement, so the same reduction finishes it)
-template <int N, int R>
+// The measurement of a tile: its P = ceil(64 / G) groups of G sites are dealt
+// to at most three work-groups, one wave per group, each summing into one of
+// the tile's three partial slots (the layout of the SU(3) measurement, so the
+// same reduction finishes it); slots that no work-group owns are zero.  One
+// group per wave, for the reason given at SiteGroups.
+template <int G>
 struct MeasShape {
-    static constexpr int G = 64 / (N / R);
-    static constexpr int WPB = G >= 64 ? 1 : (G >= 32 ? 2 : 4);
-    static constexpr int SPW = 64 / WPB;
+    static constexpr int P = (kTile + G - 1) / G;         // groups per tile
+    static constexpr int NS = P < 3 ? P : 3;              // work-groups (slots) per tile
+    static constexpr int W = (P + NS - 1) / NS;           // waves per work-group
 };
+
+// sums v over the work-group's W waves into the slot of this work-group
+template <int G>
+__device__ __forceinline__ void store_meas_partials(double v[4], double *__restrict__ partials,
+                                                    int tile, int slot) {
+    constexpr int NS = MeasShape<G>::NS, W = MeasShape<G>::W;
+    __shared__ double red[W][4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = wave_sum_d(v[k]);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < 4; k++) red[threadIdx.x >> 6][k] = v[k];
+    __syncthreads();
+    if (threadIdx.x < 4 * (1 + (slot == 0 ? 3 - NS : 0))) {
+        const int z = threadIdx.x >> 2, k = threadIdx.x & 3;   // z > 0: a slot without sites
+        double t = 0.0;
+        if (z == 0) {
+            t = red[0][k];
+#pragma unroll
+            for (int w = 1; w < W; w++) t += red[w][k];
+        }
+        partials[((size_t)tile * 3 + (z ? NS - 1 + z : slot)) * 4 + k] = t;
+    }
+}
 
 template <int N, int R>
 __global__ __launch_bounds__(256) void sun_measure_kernel(const CfgDesc *__restrict__ cfgs,
@@ -627,40 +673,22 @@ __global__ __launch_bounds__(256) void sun_measure_kernel(const CfgDesc *__restr
                                                           const MeasSlot *__restrict__ slots,
                                                           double *__restrict__ partials,
                                                           int buf_sel) {
-    const int tile = blockIdx.x;
+    constexpr int L = N / R, G = 64 / L, NS = MeasShape<G>::NS, W = MeasShape<G>::W;
+    const int tile = blockIdx.x / NS, slot = blockIdx.x - tile * NS;
     if (tile >= n_tiles) return;
     const int ci = find_cfg(tile_start, n_cfg, tile);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];     // in global memory: the twist entries are read with run-time indices
     const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
-    gptr<const v2<double>> W = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
-    constexpr int L = N / R, G = MeasShape<N, R>::G, SPW = MeasShape<N, R>::SPW;
+    gptr<const v2<double>> Wl = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int g = lane / L;
     const Grp gr{g * L, lane - g * L};
-    const int first = (tile - tile_start[ci]) * kTile + SPW * w;
+    const int s0 = (slot * W + w) * G + g;
+    const int site = (tile - tile_start[ci]) * kTile + s0;
     double v[4] = {0, 0, 0, 0};
-    for (int s0 = 0; s0 < SPW; s0 += G) {
-        const int site = first + s0 + g;
-        if (g >= G || s0 + g >= SPW || site >= c.V) continue;
-        measure_site_n<N, R>(W, c, make_geo(c, site), gr, v);
-    }
-    __shared__ double red[4][4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = wave_sum_d(v[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < 4; k++) red[w][k] = v[k];
-    __syncthreads();
-    if (threadIdx.x < 12) {
-        const int slot = threadIdx.x >> 2, k = threadIdx.x & 3;
-        double *o = partials + ((size_t)tile * 3 + slot) * 4 + k;
-        constexpr int WPB = MeasShape<N, R>::WPB;
-        const double t = WPB == 1 ? red[0][k]
-                       : WPB == 2 ? red[0][k] + red[1][k]
-                                  : (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
-        *o = slot ? 0.0 : t;
-    }
+    if (g < G && s0 < kTile && site < c.V) measure_site_n<N, R>(Wl, c, make_geo(c, site), gr, v);
+    store_meas_partials<G>(v, partials, tile, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1055,28 +1083,22 @@ __device__ __forceinline__ void sun_link_update_lds(const SunStageArgs &a, const
     store_row<N>(Wout, c.stride, mu, q.r, site, lmm_nn<N>(e, q, 1));
 }
 
-// work-group = one tile of 64 sites; wave w updates direction w for the
-// tile's sites, G at a time (lane = g N + r)
+// work-group = one group of G sites; wave w updates direction w (lane = g N + r)
 template <int N>
 __global__ __launch_bounds__(256) void sun_stage_lds_kernel(SunStageArgs a) {
     constexpr int G = LdsShape<N>::G, SLOT = LdsShape<N>::SLOT, LS = LdsShape<N>::LS;
     __shared__ v2<double> lds[4][2][SLOT];
-    const int tile = blockIdx.x;
-    if (tile >= a.n_tiles) return;
+    int ci = 0;
+    const int first = group_first<G>(a, ci);
+    if (first < 0) return;
     const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ci = find_cfg(a.tile_start, a.n_act, tile);
     const CfgDesc &c = a.cfgs[ci];   // in global memory: the twist entries are read with run-time indices
     const int lane = threadIdx.x & 63;
     const int g = lane / N;
-    if (g >= G) return;                      // lanes past the last whole link
+    const int site = first + g;
+    if (g >= G || site >= c.V) return;       // lanes past the last whole link, sites past the end
     const LaneRow<N> q{{&lds[mu][0][g * LS], &lds[mu][1][g * LS]}, lane - g * N, g * N};
-    const int first = (tile - a.tile_start[ci]) * kTile;
-#pragma unroll 1
-    for (int s0 = 0; s0 < kTile; s0 += G) {
-        const int site = first + s0 + g;
-        if (s0 + g >= kTile || site >= c.V) continue;
-        sun_link_update_lds<N>(a, c, site, mu, q);
-    }
+    sun_link_update_lds<N>(a, c, site, mu, q);
 }
 
 // measurement: own row of G_{mu nu}(n) (as clover_blk)
@@ -1180,43 +1202,24 @@ __global__ __launch_bounds__(256) void sun_measure_lds_kernel(const CfgDesc *__r
                                                               double *__restrict__ partials,
                                                               int buf_sel) {
     constexpr int G = LdsShape<N>::G, SLOT = LdsShape<N>::SLOT, LS = LdsShape<N>::LS;
-    constexpr int WPB = MeasShape<N, 1>::WPB, SPW = MeasShape<N, 1>::SPW;
-    __shared__ v2<double> lds[WPB][2][SLOT];
-    __shared__ double red[4][4];
-    const int tile = blockIdx.x;
+    constexpr int NS = MeasShape<G>::NS, W = MeasShape<G>::W;
+    __shared__ v2<double> lds[W][2][SLOT];
+    const int tile = blockIdx.x / NS, slot = blockIdx.x - tile * NS;
     if (tile >= n_tiles) return;
     const int ci = find_cfg(tile_start, n_cfg, tile);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];     // in global memory: the twist entries are read with run-time indices
     const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
-    gptr<const v2<double>> W = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
+    gptr<const v2<double>> Wl = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int g = lane / N;
     const int gg = g < G ? g : 0;            // lanes past the last link: no slot
     const LaneRow<N> q{{&lds[w][0][gg * LS], &lds[w][1][gg * LS]}, lane - g * N, g * N};
-    const int first = (tile - tile_start[ci]) * kTile + SPW * w;
+    const int s0 = (slot * W + w) * G + g;
+    const int site = (tile - tile_start[ci]) * kTile + s0;
     double v[4] = {0, 0, 0, 0};
-    if (g < G) {
-        for (int s0 = 0; s0 < SPW; s0 += G) {
-            const int site = first + s0 + g;
-            if (s0 + g >= SPW || site >= c.V) continue;
-            measure_site_lds<N>(W, c, make_geo(c, site), q, v);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = wave_sum_d(v[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < 4; k++) red[w][k] = v[k];
-    __syncthreads();
-    if (threadIdx.x < 12) {
-        const int slot = threadIdx.x >> 2, k = threadIdx.x & 3;
-        double *o = partials + ((size_t)tile * 3 + slot) * 4 + k;
-        const double t = WPB == 1 ? red[0][k]
-                       : WPB == 2 ? red[0][k] + red[1][k]
-                                  : (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
-        *o = slot ? 0.0 : t;
-    }
+    if (g < G && s0 < kTile && site < c.V) measure_site_lds<N>(Wl, c, make_geo(c, site), q, v);
+    store_meas_partials<G>(v, partials, tile, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1260,26 +1263,33 @@ int sun_variant_lds(int nc, int v) {
     return sun_code(nc, v) == kLds ? 1 : 0;
 }
 
+// links (sites) a wave holds: R rows per lane, or the LDS-operand variant's one
+template <int N, int R>
+constexpr int links_per_wave() {
+    return 64 / (R == kLds ? N : N / (R == kLds ? 1 : R));
+}
+
 template <int N, int R>
 static hipError_t stage_nr(hipStream_t s, const SunStageArgs &a) {
+    const dim3 grid((a.n_tiles * SiteGroups<links_per_wave<N, R>()>::P + 7) / 8 * 8);
     if constexpr (R == kLds)
-        hipLaunchKernelGGL((sun_stage_lds_kernel<N>), dim3(a.n_tiles), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((sun_stage_lds_kernel<N>), grid, dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL((sun_stage_kernel<N, R>), dim3(a.n_tiles), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((sun_stage_kernel<N, R>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 template <int N, int R>
 static hipError_t measure_nr(hipStream_t s, const CfgDesc *cfgs, const int *tile_start, int n_cfg,
                              int n_tiles, const MeasSlot *slots, double *partials, int buf_sel) {
+    typedef MeasShape<links_per_wave<N, R>()> Sh;
+    const dim3 grid(n_tiles * Sh::NS), block(64 * Sh::W);
     if constexpr (R == kLds)
-        hipLaunchKernelGGL((sun_measure_lds_kernel<N>), dim3(n_tiles),
-                           dim3(64 * MeasShape<N, 1>::WPB), 0, s, cfgs, tile_start, n_cfg, n_tiles,
-                           slots, partials, buf_sel);
+        hipLaunchKernelGGL((sun_measure_lds_kernel<N>), grid, block, 0, s, cfgs, tile_start, n_cfg,
+                           n_tiles, slots, partials, buf_sel);
     else
-        hipLaunchKernelGGL((sun_measure_kernel<N, R>), dim3(n_tiles),
-                           dim3(64 * MeasShape<N, R>::WPB), 0, s, cfgs, tile_start, n_cfg, n_tiles,
-                           slots, partials, buf_sel);
+        hipLaunchKernelGGL((sun_measure_kernel<N, R>), grid, block, 0, s, cfgs, tile_start, n_cfg,
+                           n_tiles, slots, partials, buf_sel);
     return hipGetLastError();
 }
 
