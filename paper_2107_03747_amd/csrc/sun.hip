@@ -405,45 +405,202 @@ __device__ __forceinline__ Blk<N, R> proj_ah_blk(const Blk<N, R> &m, const Grp &
     return a;
 }
 
-// exp(X) for X anti-Hermitian: scale so that ||Y||_F <= 1/4 (Y = X 2^-s),
-// degree-12 Taylor polynomial by Horner's rule as T <- 1 + T Y / k (T is a
-// polynomial in Y, so T Y = Y T), then s squarings.  Truncation error
-// ||Y||^13 / 13! < 3e-18.
-template <int N, int R>
-__device__ __forceinline__ Blk<N, R> exp_blk(const Blk<N, R> &x, const Grp &g) {
-    double n2 = 0.0;
-#pragma unroll
-    for (int i = 0; i < R; i++)
-#pragma unroll
-        for (int j = 0; j < N; j++)
-            n2 = fma(x.e[i][j].x, x.e[i][j].x, fma(x.e[i][j].y, x.e[i][j].y, n2));
-    const double nrm = sqrt(group_sum<N, R>(n2, g));
+// exp(X) - 1 for X anti-Hermitian and traceless (the identity is left out, so
+// that the caller forms exp(X) U as U + (exp(X) - 1) U).  The exponential is
+// the part of a stage that a better formula shortens, the staples are fixed:
+//   N = 2   X^2 = -theta^2 1: exp(X) - 1 = (cos theta - 1) 1 + (sin theta / theta) X,
+//           no product at all;
+//   N = 3   Cayley-Hamilton, X^3 = p X + d 1: one product (X^2), then a series
+//           of three coefficients;
+//   N >= 4  a Taylor polynomial of degree 3 q + 2 in the grouping of Paterson
+//           and Stockmeyer, B_0 + Y^3 (B_1 + Y^3 (B_2 + ...)) with
+//           B_j = sum_{i<3} Y^(3j+i) / (3j+i)!: q + 2 products.
+// q is the least whose remainder theta^(3q+3) / (3q+3)! is below 2.8e-17
+// (theta = ||X||_F; a flow step of eps = 0.01 has theta of 0.01 to 0.06, q = 2,
+// four products where Horner's rule at degree 12 took eleven); above theta =
+// 1.4 the argument is halved s times and the result squared.  Each link's own
+// norm decides, so a link's result does not depend on its neighbours in a wave.
+struct ExpPlan {
+    int q, s;
+    double f;   // 2^-s
+};
+__device__ __forceinline__ ExpPlan exp_plan(double theta) {
+    ExpPlan p{2, 0, 1.0};
+    if (theta > 1.4) {
+        p.s = min((int)ceil(log2(theta * (1.0 / 1.4))), 60);
+        p.f = ldexp(1.0, -p.s);
+        theta *= p.f;
+    }
+    p.q = theta <= 0.059 ? 2 : theta <= 0.21 ? 3 : theta <= 0.49 ? 4 : theta <= 0.88 ? 5 : 6;
+    return p;
+}
+__constant__ double kInvFact[21] = {
+    1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320,
+    1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800,
+    1.0 / 87178291200, 1.0 / 1307674368000, 1.0 / 20922789888000, 1.0 / 355687428096000,
+    1.0 / 6402373705728000, 1.0 / 121645100408832000, 1.0 / 2432902008176640000};
+
+// cos(theta) - 1 and sin(theta) / theta from t2 = theta^2: the series for
+// theta <= 1/2 (remainder 0.5^18 / 18! < 1e-21), the double-angle formulas above
+__device__ __forceinline__ void cosm1_sinc(double t2, double &cm, double &sn) {
     int s = 0;
-    if (nrm > 0.25) s = (int)ceil(log2(nrm * 4.0));
-    const double f = ldexp(1.0, -s);
-    constexpr int M = 12;
-    Blk<N, R> y, t;
+    while (t2 > 0.25 && s < 60) {
+        t2 *= 0.25;
+        s++;
+    }
+    // cos - 1 = -t2/2 (1 - t2/12 (1 - t2/30 (...))), sinc = 1 - t2/6 (1 - t2/20 (...))
+    double c = 1.0, n = 1.0;
+#pragma unroll
+    for (int k = 8; k >= 2; k--) c = fma(-t2 * (1.0 / ((2 * k - 1) * (2 * k))), c, 1.0);
+#pragma unroll
+    for (int k = 8; k >= 1; k--) n = fma(-t2 * (1.0 / ((2 * k) * (2 * k + 1))), n, 1.0);
+    c *= -0.5 * t2;
+    for (int i = 0; i < s; i++) {
+        n = fma(n, c, n);                 // sin 2x / 2x = (sin x / x) cos x
+        c = 2.0 * fma(c, c, 2.0 * c);     // cos 2x - 1 = 2 (cos x - 1)^2 + 4 (cos x - 1)
+    }
+    cm = c;
+    sn = n;
+}
+
+// Coefficients of exp(X) - 1 = f0 + f1 X + f2 X^2 for a 3 x 3 X with
+// ||X|| <= 1, X^3 = p X + i d: the k-th term of the series is
+// a + b X + c X^2, the next (i d c, a + p c, b) / k; 18 terms (1/19! = 8e-18).
+__device__ __forceinline__ void exp3_coeffs(double p, double d, cx<double> &f0, cx<double> &f1,
+                                            cx<double> &f2) {
+    cx<double> a = {1.0, 0.0}, b = {0.0, 0.0}, c = {0.0, 0.0};
+    f0 = f1 = f2 = {0.0, 0.0};
+#pragma unroll
+    for (int k = 1; k <= 18; k++) {
+        const double r = kInvK[k];
+        const cx<double> na = {-d * c.y * r, d * c.x * r};
+        const cx<double> nb = {fma(p, c.x, a.x) * r, fma(p, c.y, a.y) * r};
+        c = {b.x * r, b.y * r};
+        a = na;
+        b = nb;
+        f0 = cadd(f0, a);
+        f1 = cadd(f1, b);
+        f2 = cadd(f2, c);
+    }
+}
+
+// own rows of a + b X + c X^2 with complex or real coefficients
+template <int N, int R>
+__device__ __forceinline__ Blk<N, R> poly3(cx<double> f0, cx<double> f1, cx<double> f2,
+                                           const Blk<N, R> &x, const Blk<N, R> &x2, const Grp &g) {
+    Blk<N, R> o;
 #pragma unroll
     for (int i = 0; i < R; i++)
 #pragma unroll
         for (int j = 0; j < N; j++) {
-            y.e[i][j] = {f * x.e[i][j].x, f * x.e[i][j].y};
-            t.e[i][j] = {y.e[i][j].x * (1.0 / M), y.e[i][j].y * (1.0 / M)};
-            if (j == row_index<N, R>(g, i)) t.e[i][j].x += 1.0;
+            o.e[i][j] = cmadd(cmul(f1, x.e[i][j]), f2, x2.e[i][j]);
+            if (j == row_index<N, R>(g, i)) o.e[i][j] = cadd(o.e[i][j], f0);
         }
-    for (int k = M - 1; k >= 1; k--) {
-        const Blk<N, R> ty = mm_nn<N, R>(t, y, g);
-        const double ik = 1.0 / (double)k;
+    return o;
+}
+template <int N, int R>
+__device__ __forceinline__ Blk<N, R> poly3(double f0, double f1, double f2, const Blk<N, R> &x,
+                                           const Blk<N, R> &x2, const Grp &g) {
+    Blk<N, R> o;
+#pragma unroll
+    for (int i = 0; i < R; i++)
+#pragma unroll
+        for (int j = 0; j < N; j++) {
+            o.e[i][j] = {fma(f2, x2.e[i][j].x, f1 * x.e[i][j].x),
+                         fma(f2, x2.e[i][j].y, f1 * x.e[i][j].y)};
+            if (j == row_index<N, R>(g, i)) o.e[i][j].x += f0;
+        }
+    return o;
+}
+
+template <int N, int R>
+__device__ __forceinline__ void blk_scale(Blk<N, R> &x, double f) {
+#pragma unroll
+    for (int i = 0; i < R; i++)
+#pragma unroll
+        for (int j = 0; j < N; j++) x.e[i][j] = {f * x.e[i][j].x, f * x.e[i][j].y};
+}
+
+// sum over the whole matrix of Re(a conj(b)) and of Im(a conj(b))
+template <int N, int R>
+__device__ __forceinline__ double re_dot(const Blk<N, R> &a, const Blk<N, R> &b, const Grp &g) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < R; i++)
+#pragma unroll
+        for (int j = 0; j < N; j++)
+            s = fma(a.e[i][j].x, b.e[i][j].x, fma(a.e[i][j].y, b.e[i][j].y, s));
+    return group_sum<N, R>(s, g);
+}
+template <int N, int R>
+__device__ __forceinline__ double im_dot(const Blk<N, R> &a, const Blk<N, R> &b, const Grp &g) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < R; i++)
+#pragma unroll
+        for (int j = 0; j < N; j++)
+            s = fma(a.e[i][j].y, b.e[i][j].x, fma(-a.e[i][j].x, b.e[i][j].y, s));
+    return group_sum<N, R>(s, g);
+}
+
+template <int N, int R>
+__device__ __forceinline__ Blk<N, R> expm1_blk(Blk<N, R> x, const Grp &g) {
+    const double n2 = re_dot<N, R>(x, x, g);
+    Blk<N, R> t;
+    if constexpr (N == 2) {
+        double cm, sn;
+        cosm1_sinc(0.5 * n2, cm, sn);
+        blk_scale<N, R>(x, sn);
 #pragma unroll
         for (int i = 0; i < R; i++)
 #pragma unroll
-            for (int j = 0; j < N; j++) {
-                t.e[i][j] = {ty.e[i][j].x * ik, ty.e[i][j].y * ik};
-                if (j == row_index<N, R>(g, i)) t.e[i][j].x += 1.0;
-            }
+            for (int j = 0; j < N; j++)
+                if (j == row_index<N, R>(g, i)) x.e[i][j].x += cm;
+        return x;
+    } else if constexpr (N == 3) {
+        const double theta = sqrt(n2);
+        int s = 0;
+        double f = 1.0;
+        if (theta > 1.0) {
+            s = min((int)ceil(log2(theta)), 60);
+            f = ldexp(1.0, -s);
+            blk_scale<N, R>(x, f);
+        }
+        const Blk<N, R> x2 = mm_nn<N, R>(x, x, g);
+        // p = Tr X^2 / 2 = -||X||^2 / 2; det X = Tr X^3 / 3 = i d,
+        // Tr X^3 = -sum X^2_ij conj(X_ij)
+        cx<double> f0, f1, f2;
+        exp3_coeffs(-0.5 * n2 * f * f, im_dot<N, R>(x2, x, g) * (-1.0 / 3.0), f0, f1, f2);
+        t = poly3<N, R>(f0, f1, f2, x, x2, g);
+        for (int i = 0; i < s; i++) {
+            Blk<N, R> d2 = mm_nn<N, R>(t, t, g);
+            blk_axpy(d2, cx<double>{2.0, 0.0}, t);
+            t = d2;
+        }
+        return t;
+    } else {
+        const ExpPlan pl = exp_plan(sqrt(n2));
+        if (pl.s) blk_scale<N, R>(x, pl.f);
+        const Blk<N, R> x2 = mm_nn<N, R>(x, x, g);
+        const Blk<N, R> x3 = mm_nn<N, R>(x2, x, g);
+        const double *k = kInvFact + 3 * pl.q;
+        t = poly3<N, R>(k[0], k[1], k[2], x, x2, g);
+        for (int j = pl.q - 1; j >= 0; j--) {
+            const Blk<N, R> m = mm_nn<N, R>(t, x3, g);
+            k = kInvFact + 3 * j;
+            t = poly3<N, R>(j ? k[0] : 0.0, k[1], k[2], x, x2, g);
+#pragma unroll
+            for (int i = 0; i < R; i++)
+#pragma unroll
+                for (int c = 0; c < N; c++) t.e[i][c] = cadd(t.e[i][c], m.e[i][c]);
+        }
+        for (int i = 0; i < pl.s; i++) {
+            Blk<N, R> d2 = mm_nn<N, R>(t, t, g);
+            blk_axpy(d2, cx<double>{2.0, 0.0}, t);
+            t = d2;
+        }
+        return t;
     }
-    for (int i = 0; i < s; i++) t = mm_nn<N, R>(t, t, g);
-    return t;
 }
 
 struct SunStageArgs {
@@ -476,8 +633,9 @@ __device__ __forceinline__ void sun_link_update(const SunStageArgs &a, const Cfg
         blk_axpy(z, cx<double>{kSunRkA[a.stage], 0.0}, xo);
     }
     if (a.stage < 2) store_blk<N, R>(X, c.stride, MU, gr, site, z);
-    const Blk<N, R> e = exp_blk<N, R>(z, gr);
-    store_blk<N, R>(Wout, c.stride, MU, gr, site, mm_nn<N, R>(e, U, gr));
+    Blk<N, R> n = mm_nn<N, R>(expm1_blk<N, R>(z, gr), U, gr);
+    blk_axpy(n, cx<double>{1.0, 0.0}, U);
+    store_blk<N, R>(Wout, c.stride, MU, gr, site, n);
 }
 
 // Site groups of the stage launches.  A wave holds G = 64 / L sites; the sites
@@ -1025,38 +1183,49 @@ __device__ __forceinline__ Row<N> proj_ah_row(const Row<N> &m, const LaneRow<N> 
     return a;
 }
 
-// exp(X), X anti-Hermitian: the scaling, degree and squarings of exp_blk; the
-// scaled argument Y stays in slot 0 for the whole Horner loop
+// own row of f0 + f1 X + f2 X^2
 template <int N>
-__device__ __forceinline__ Row<N> exp_row(const Row<N> &x, const LaneRow<N> &q) {
+__device__ __forceinline__ Row<N> poly3_row(double f0, double f1, double f2, const Row<N> &x,
+                                            const Row<N> &x2, int r) {
+    Row<N> o;
+#pragma unroll
+    for (int j = 0; j < N; j++) {
+        o.e[j] = {fma(f2, x2.e[j].x, f1 * x.e[j].x), fma(f2, x2.e[j].y, f1 * x.e[j].y)};
+        if (j == r) o.e[j].x += f0;
+    }
+    return o;
+}
+
+// exp(X) - 1, X anti-Hermitian: the polynomial of expm1_blk (N >= 4) for every
+// N; X, then X^3, stay in slot 0
+template <int N>
+__device__ __forceinline__ Row<N> expm1_row(Row<N> x, const LaneRow<N> &q) {
     double n2 = 0.0;
 #pragma unroll
     for (int j = 0; j < N; j++) n2 = fma(x.e[j].x, x.e[j].x, fma(x.e[j].y, x.e[j].y, n2));
-    const double nrm = sqrt(link_sum<N>(n2, q));
-    int s = 0;
-    if (nrm > 0.25) s = (int)ceil(log2(nrm * 4.0));
-    const double f = ldexp(1.0, -s);
-    constexpr int M = 12;
-    Row<N> y, t;
+    const ExpPlan pl = exp_plan(sqrt(link_sum<N>(n2, q)));
+    if (pl.s)
 #pragma unroll
-    for (int j = 0; j < N; j++) {
-        y.e[j] = {f * x.e[j].x, f * x.e[j].y};
-        t.e[j] = {y.e[j].x * (1.0 / M), y.e[j].y * (1.0 / M)};
-        if (j == q.r) t.e[j].x += 1.0;
-    }
-    put(q, 0, y);
-    for (int k = M - 1; k >= 1; k--) {
-        const Row<N> ty = lmm_nn<N>(t, q, 0);
-        const double ik = 1.0 / (double)k;
+        for (int j = 0; j < N; j++) x.e[j] = {pl.f * x.e[j].x, pl.f * x.e[j].y};
+    put(q, 0, x);
+    const Row<N> x2 = lmm_nn<N>(x, q, 0);
+    put(q, 0, lmm_nn<N>(x2, q, 0));
+    const double *k = kInvFact + 3 * pl.q;
+    Row<N> t = poly3_row<N>(k[0], k[1], k[2], x, x2, q.r);
+#pragma unroll 1
+    for (int j = pl.q - 1; j >= 0; j--) {
+        const Row<N> m = lmm_nn<N>(t, q, 0);
+        k = kInvFact + 3 * j;
+        t = poly3_row<N>(j ? k[0] : 0.0, k[1], k[2], x, x2, q.r);
 #pragma unroll
-        for (int j = 0; j < N; j++) {
-            t.e[j] = {ty.e[j].x * ik, ty.e[j].y * ik};
-            if (j == q.r) t.e[j].x += 1.0;
-        }
+        for (int c = 0; c < N; c++) t.e[c] = cadd(t.e[c], m.e[c]);
     }
-    for (int i = 0; i < s; i++) {
+#pragma unroll 1
+    for (int i = 0; i < pl.s; i++) {
         put(q, 1, t);
-        t = lmm_nn<N>(t, q, 1);
+        Row<N> d2 = lmm_nn<N>(t, q, 1);
+        row_axpy(d2, cx<double>{2.0, 0.0}, t);
+        t = d2;
     }
     return t;
 }
@@ -1078,9 +1247,12 @@ __device__ __forceinline__ void sun_link_update_lds(const SunStageArgs &a, const
         row_axpy(z, cx<double>{kSunRkA[a.stage], 0.0}, xo);
     }
     if (a.stage < 2) store_row<N>(X, c.stride, mu, q.r, site, z);
-    const Row<N> e = exp_row<N>(z, q);
+    const Row<N> e = expm1_row<N>(z, q);
     put(q, 1, U);
-    store_row<N>(Wout, c.stride, mu, q.r, site, lmm_nn<N>(e, q, 1));
+    Row<N> n = lmm_nn<N>(e, q, 1);
+#pragma unroll
+    for (int j = 0; j < N; j++) n.e[j] = cadd(n.e[j], U.e[j]);
+    store_row<N>(Wout, c.stride, mu, q.r, site, n);
 }
 
 // work-group = one group of G sites; wave w updates direction w (lane = g N + r)
