@@ -367,9 +367,8 @@ def sun_mode(tgf, torch, args):
     v = f.autotune(None) if args.variant is None else args.variant
     f.set_variant(v)
     rows_per_lane = int(tgf.tgf_sun_rows_per_lane(N, v))
-    lds = int(tgf.tgf_sun_variant_lds(N, v)) == 1
-    log(f"SU({N}): variant {v} ({rows_per_lane} rows per lane, "
-        f"{'LDS operands' if lds else 'permutes'})")
+    operands = ("permutes", "lds", "matrix cores")[int(tgf.tgf_sun_variant_lds(N, v))]
+    log(f"SU({N}): variant {v} ({rows_per_lane} rows per lane, operands: {operands})")
     f.flow(EPS, t_end, 0.0)                      # warm-up (graph capture)
     times = []
     for _ in range(max(1, args.steps // 5)):
@@ -399,9 +398,11 @@ def sun_mode(tgf, torch, args):
                    "n_configs": n_cfg, "sites": n_cfg * V},
         "t2E_last_cfg0": float(rows[-1, 0, 2]),
         "rows_per_lane": rows_per_lane,
-        "operands": "lds" if lds else "permutes",
-        "roofline": {"kernel": (f"sun_stage_lds_kernel<{N}>" if lds
-                                else f"sun_stage_kernel<{N}, {rows_per_lane}>"), "bound": "alu",
+        "operands": operands,
+        "roofline": {"kernel": {"lds": f"sun_stage_lds_kernel<{N}>",
+                                "matrix cores": f"sun_stage_mfma_kernel<{N}>"}.get(
+                                    operands, f"sun_stage_kernel<{N}, {rows_per_lane}>"),
+                     "bound": "alu",
                      "achieved": round(tflops, 3), "peak": round(ALU_PEAK_TFLOPS, 1),
                      "unit": "TFLOP/s", "frac": round(tflops / ALU_PEAK_TFLOPS, 4),
                      "hbm_gbs_algorithmic": round(gbs, 1),

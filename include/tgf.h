@@ -150,16 +150,19 @@ tgf_status tgf_create(tgf_ctx **out, int32_t n_cfg, const tgf_geom *geoms, tgf_s
  *     spread over nc / rows lanes, rows = nc: one thread per link), and how a
  *     product reaches the rows other lanes hold: cross-lane permutes, or (the
  *     LDS-operand variant, one row per lane) a per-wave LDS copy of the right
- *     operand; tgf_set_variant accepts -1 .. tgf_sun_variant_count(nc) - 1 and
+ *     operand; or (nc = 4, 7, 8, the default there) one entry per lane and the
+ *     products on the matrix cores;
+ *     tgf_set_variant accepts -1 .. tgf_sun_variant_count(nc) - 1 and
  *     tgf_autotune times them; tgf_mc and tgf_slice_charge return
  *     TGF_E_UNSUPPORTED.
  * tgf_workspace_bytes_sun returns 0 on invalid arguments. */
 size_t tgf_workspace_bytes_sun(int32_t nc, int32_t n_cfg, const tgf_geom *geoms,
                                tgf_storage st);
 /* Number of SU(nc) stage variants (0 for nc outside 2..8), the matrix rows
- * per lane of variant v (-1 = the default, 0; returns 0 for no such variant),
- * and whether v reads product operands from LDS (1) or through cross-lane
- * permutes (0; -1 for no such variant). */
+ * per lane of variant v (-1 = the default, 0; 1 for the matrix-core variant;
+ * returns 0 for no such variant), and whether v reads product operands from
+ * LDS (1) or through cross-lane permutes (0), or multiplies on the matrix
+ * cores (2); -1 for no such variant. */
 int32_t tgf_sun_variant_count(int32_t nc);
 int32_t tgf_sun_rows_per_lane(int32_t nc, int32_t variant);
 int32_t tgf_sun_variant_lds(int32_t nc, int32_t variant);
@@ -204,8 +207,8 @@ tgf_status tgf_densities(tgf_ctx *c, int32_t cfg, double *e_dev, double *q_dev);
 
 /* Where cfg's links are stored now: *offset = byte offset within the
  * workspace, *bytes = size of that storage buffer (structure of arrays
- * [mu][entry][site], FP32 entries paired; the layout is internal to the
- * library).  For callers that checksum, snapshot or poison the stored field in
+ * [mu][entry][site], FP32 entries paired; SU(4), SU(7) and SU(8) contexts
+ * [mu][site][entry]; the layout is internal to the library).  For callers that checksum, snapshot or poison the stored field in
  * place; the buffer alternates with every RK stage, so the answer holds until
  * the next tgf_flow or tgf_load_links*.  TGF_E_STATE if cfg is not loaded. */
 tgf_status tgf_link_buffer(tgf_ctx *c, int32_t cfg, size_t *offset, size_t *bytes);

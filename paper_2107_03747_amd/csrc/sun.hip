@@ -30,6 +30,7 @@
 #include "lattice_dev.h"
 #include "layout.h"
 #include "su3_dev.h"
+#include "sun_dev.h"
 
 namespace tgf {
 
@@ -205,11 +206,6 @@ __device__ __forceinline__ void blk_axpy(Blk<N, R> &y, cx<double> z, const Blk<N
 // base, the lane part a 32-bit byte offset (sites per configuration are capped
 // so that the N^2 planes of one direction span less than 4 GiB)
 
-template <int N>
-__device__ __forceinline__ unsigned row_off(int r, int j, int stride, int site) {
-    return ((unsigned)(r * N + j) * (unsigned)stride + (unsigned)site) * 16u;
-}
-
 // SGPR plane base + 32-bit lane offset for every access (sgpr_base,
 // lane_here, no 64-bit per-lane address arithmetic) where it measured
 // faster over a whole flow: (4,4) +31%, (6,2) +10%, (7,1) +3%; the other
@@ -259,80 +255,6 @@ __device__ __forceinline__ void store_blk(gptr<v2<double>> W, int stride, int mu
             for (int j = 0; j < N; j++)
                 st(q, row_off<N>(row_index<N, R>(g, i), j, stride, site), v.e[i][j]);
     }
-}
-
-// twist exponent n_{mu nu} (mod N, antisymmetric) and Z = exp(2 pi i n / N)
-template <int N>
-__device__ __forceinline__ int tw_exp(const CfgDesc &c, int mu, int nu) {
-    if (mu < nu) return c.tw[plane_index(mu, nu)];
-    const int t = c.tw[plane_index(nu, mu)];
-    return t ? N - t : 0;
-}
-
-// exp(2 pi i k / N) for N = 2..8, k = 0..N-1 as (cos, sin), the exact values
-// rounded to double (evaluated to 60 digits; zeros and units exact).  A table
-// read with a wave-uniform index keeps the trigonometric code, and the private
-// memory its argument reduction uses, out of the flow kernels.
-__constant__ double kTwistPhase[9][8][2] = {
-    {  // unused
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // unused
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // N = 2
-        {1.0, 0.0}, {-1.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // N = 3
-        {1.0, 0.0}, {-0.5, 0.8660254037844386},
-        {-0.5, -0.8660254037844386}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // N = 4
-        {1.0, 0.0}, {0.0, 1.0},
-        {-1.0, 0.0}, {0.0, -1.0},
-        {0.0, 0.0}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // N = 5
-        {1.0, 0.0}, {0.30901699437494745, 0.9510565162951535},
-        {-0.8090169943749475, 0.5877852522924731}, {-0.8090169943749475, -0.5877852522924731},
-        {0.30901699437494745, -0.9510565162951535}, {0.0, 0.0},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // N = 6
-        {1.0, 0.0}, {0.5, 0.8660254037844386},
-        {-0.5, 0.8660254037844386}, {-1.0, 0.0},
-        {-0.5, -0.8660254037844386}, {0.5, -0.8660254037844386},
-        {0.0, 0.0}, {0.0, 0.0},
-    },
-    {  // N = 7
-        {1.0, 0.0}, {0.6234898018587335, 0.7818314824680298},
-        {-0.2225209339563144, 0.9749279121818236}, {-0.9009688679024191, 0.4338837391175581},
-        {-0.9009688679024191, -0.4338837391175581}, {-0.2225209339563144, -0.9749279121818236},
-        {0.6234898018587335, -0.7818314824680298}, {0.0, 0.0},
-    },
-    {  // N = 8
-        {1.0, 0.0}, {0.7071067811865476, 0.7071067811865476},
-        {0.0, 1.0}, {-0.7071067811865476, 0.7071067811865476},
-        {-1.0, 0.0}, {-0.7071067811865476, -0.7071067811865476},
-        {0.0, -1.0}, {0.7071067811865476, -0.7071067811865476},
-    },
-};
-
-template <int N>
-__device__ __forceinline__ cx<double> zphase(int t) {
-    return {kTwistPhase[N][t][0], kTwistPhase[N][t][1]};
 }
 
 // ---------------------------------------------------------------------------
@@ -420,26 +342,6 @@ __device__ __forceinline__ Blk<N, R> proj_ah_blk(const Blk<N, R> &m, const Grp &
 // four products where Horner's rule at degree 12 took eleven); above theta =
 // 1.4 the argument is halved s times and the result squared.  Each link's own
 // norm decides, so a link's result does not depend on its neighbours in a wave.
-struct ExpPlan {
-    int q, s;
-    double f;   // 2^-s
-};
-__device__ __forceinline__ ExpPlan exp_plan(double theta) {
-    ExpPlan p{2, 0, 1.0};
-    if (theta > 1.4) {
-        p.s = min((int)ceil(log2(theta * (1.0 / 1.4))), 60);
-        p.f = ldexp(1.0, -p.s);
-        theta *= p.f;
-    }
-    p.q = theta <= 0.059 ? 2 : theta <= 0.21 ? 3 : theta <= 0.49 ? 4 : theta <= 0.88 ? 5 : 6;
-    return p;
-}
-__constant__ double kInvFact[21] = {
-    1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320,
-    1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800,
-    1.0 / 87178291200, 1.0 / 1307674368000, 1.0 / 20922789888000, 1.0 / 355687428096000,
-    1.0 / 6402373705728000, 1.0 / 121645100408832000, 1.0 / 2432902008176640000};
-
 // cos(theta) - 1 and sin(theta) / theta from t2 = theta^2: the series for
 // theta <= 1/2 (remainder 0.5^18 / 18! < 1e-21), the double-angle formulas above
 __device__ __forceinline__ void cosm1_sinc(double t2, double &cm, double &sn) {
@@ -603,19 +505,6 @@ __device__ __forceinline__ Blk<N, R> expm1_blk(Blk<N, R> x, const Grp &g) {
     }
 }
 
-struct SunStageArgs {
-    const CfgDesc *cfgs;
-    const int *tile_start;
-    int n_act;
-    int n_tiles;
-    int step;
-    int stage;
-    double eps;
-};
-
-__constant__ double kSunRkA[3] = {0.0, -17.0 / 9.0, -1.0};
-__constant__ double kSunRkB[3] = {0.25, 8.0 / 9.0, 0.75};
-
 template <int N, int R, int MU>
 __device__ __forceinline__ void sun_link_update(const SunStageArgs &a, const CfgDesc &c, int site,
                                                 const Grp &gr) {
@@ -636,33 +525,6 @@ __device__ __forceinline__ void sun_link_update(const SunStageArgs &a, const Cfg
     Blk<N, R> n = mm_nn<N, R>(expm1_blk<N, R>(z, gr), U, gr);
     blk_axpy(n, cx<double>{1.0, 0.0}, U);
     store_blk<N, R>(Wout, c.stride, MU, gr, site, n);
-}
-
-// Site groups of the stage launches.  A wave holds G = 64 / L sites; the sites
-// of a configuration are cut into groups of G, and every group is a work-group
-// of its own (wave w updates direction w).  ceil(64 / G) work-groups are
-// launched per 64-site tile, enough for every group of the configuration; the
-// few past its end return.  One group per work-group, not a loop over a tile's
-// groups: a 3x3x15x15 SU(5) box is 169 work-groups of one group instead of 32
-// of six in a row (a 16-step flow 7.2 -> 1.8 ms; 4x4x20x20 boxes of 102k sites
-// -19%), and no group is cut at a tile's end.  The launch order gives each XCD
-// one contiguous range of groups.
-template <int G>
-struct SiteGroups {
-    static constexpr int P = (kTile + G - 1) / G;   // work-groups per tile
-};
-
-// site of lane 0 of the group that work-group b takes (-1: none) and its configuration
-template <int G>
-__device__ __forceinline__ int group_first(const SunStageArgs &a, int &ci) {
-    constexpr int P = SiteGroups<G>::P;
-    const int nb = a.n_tiles * P;
-    const int b = remap_block(blockIdx.x, nb, 1);
-    if (b >= nb) return -1;
-    const int tile = b / P;
-    ci = find_cfg(a.tile_start, a.n_act, tile);
-    const int first = (b - a.tile_start[ci] * P) * G;
-    return first < a.cfgs[ci].V ? first : -1;
 }
 
 template <int N, int R>
@@ -689,13 +551,6 @@ __global__ __launch_bounds__(256) void sun_stage_kernel(SunStageArgs a) {
 // ---------------------------------------------------------------------------
 // measurement: clover G (eq. gmunu) from the four twisted leaves, e(n),
 // q(n) = (1/4 pi^2)[Tr G01 G23 - Tr G02 G13 + Tr G03 G12], plaquette and action
-
-template <int N>
-__device__ __forceinline__ cx<double> leaf_phase(const CfgDesc &c, int mu, int nu, int xm, int xn) {
-    const int k = tw_exp<N>(c, mu, nu);
-    if (k && xm == 0 && xn == 0) return cconj(zphase<N>(k));
-    return {1.0, 0.0};
-}
 
 // own rows of G_{mu nu}(n); rp += Re of this lane's diagonal entries of Z^* P_{mu nu}(n)
 template <int N, int R>
@@ -782,12 +637,6 @@ __device__ __forceinline__ void measure_site_n(gptr<const v2<double>> W, const C
     v[3] += 6.0 * R - p;   // this lane's share of sum_planes (N - Re Tr Z^* P)
 }
 
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 // The measurement of a tile: its P = ceil(64 / G) groups of G sites are dealt
 // to at most three work-groups, one wave per group, each summing into one of
 // the tile's three partial slots (the layout of the SU(3) measurement, so the
@@ -869,6 +718,23 @@ __global__ void sun_unpack_kernel(const double2 *__restrict__ W, double2 *__rest
     dst[((size_t)i * 4 + mu) * nn + e] = W[(size_t)me * stride + i];
 }
 
+// the same with storage [mu][site][entry]: thread k moves entry k of the
+// canonical order, so both sides are contiguous over a link
+__global__ void sun_pack_aos_kernel(const double2 *__restrict__ src, double2 *__restrict__ W,
+                                    size_t n, int stride, int nn) {
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const size_t link = k / nn, i = link >> 2;
+    W[(((link & 3) * stride) + i) * nn + (k - link * nn)] = src[k];
+}
+__global__ void sun_unpack_aos_kernel(const double2 *__restrict__ W, double2 *__restrict__ dst,
+                                      size_t n, int stride, int nn) {
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const size_t link = k / nn, i = link >> 2;
+    dst[k] = W[(((link & 3) * stride) + i) * nn + (k - link * nn)];
+}
+
 // max |U U^+ - 1| and |det U - 1| for one link held whole by one thread;
 // the determinant by Gaussian elimination with partial pivoting
 template <int N>
@@ -939,7 +805,7 @@ __global__ __launch_bounds__(64) void sun_check_kernel(const void *__restrict__ 
 #pragma unroll
                 for (int j = 0; j < N; j++) {
                     const double2 v = CANON ? s[((size_t)i * 4 + mu) * N * N + r * N + j]
-                                            : s[((size_t)(mu * N * N + r * N + j)) * stride + i];
+                                            : s[sun_index<N>(mu, r * N + j, stride, i)];
                     a[r][j] = {v.x, v.y};
                 }
             sun_defects<N>(a, du, dd);
@@ -1395,29 +1261,31 @@ __global__ __launch_bounds__(256) void sun_measure_lds_kernel(const CfgDesc *__r
 }
 
 // ---------------------------------------------------------------------------
-// launchers.  The variants of each N in order (variant 0 is the default):
-// the first entry is the fastest measured on the benchmark boxes (about 10^6
-// sites of 4x4x4Nx4N, stage launch): one thread per link for N = 2..4, the
-// LDS-operand variant from N = 5 (3.1x to 8.1x the permute variants there).
+// launchers.  The variants of each N in order (variant 0 is the default, the
+// fastest measured): products on the matrix cores for N = 4, 7, 8 (sun_mfma.hip),
+// one thread per link for N = 2, 3, LDS operands for N = 5, 6 (whose matrices
+// would fill 24% and 42% of the matrix instructions' 8 x 8 x 8).
 
-// Variant table: rows per lane of the permute variants, or kLds for the
-// LDS-operand variant (one row per lane).
-constexpr int kLds = 16;
+// Variant table: rows per lane of the permute variants, kLds for the
+// LDS-operand variant (one row per lane), kMx for the matrix cores.
+constexpr int kLds = 16, kMx = 17;
 
 __host__ __device__ constexpr int sun_code(int nc, int v) {
-    // N = 2: 2, 1, LDS    3: 3, 1, LDS    4: 4, 2, 1, LDS    5, 7, 8: LDS, 1    6: LDS, 2, 1
+    // N = 2: 2, 1, LDS    3: 3, 1, LDS    4: Mx, 4, 2, 1, LDS    5: LDS, 1    6: LDS, 2, 1
+    // 7, 8: Mx, LDS, 1
     return nc == 2 ? (v == 0 ? 2 : (v == 1 ? 1 : kLds))
          : nc == 3 ? (v == 0 ? 3 : (v == 1 ? 1 : kLds))
-         : nc == 4 ? (v == 0 ? 4 : (v == 1 ? 2 : (v == 2 ? 1 : kLds)))
+         : nc == 4 ? (v == 0 ? kMx : (v == 1 ? 4 : (v == 2 ? 2 : (v == 3 ? 1 : kLds))))
+         : nc == 5 ? (v == 0 ? kLds : 1)
          : nc == 6 ? (v == 0 ? kLds : (v == 1 ? 2 : 1))
-         : (v == 0 ? kLds : 1);
+         : (v == 0 ? kMx : (v == 1 ? kLds : 1));
 }
 
 int sun_variant_count(int nc) {
     switch (nc) {
-        case 2: case 3: case 6: return 3;
-        case 4: return 4;
-        case 5: case 7: case 8: return 2;
+        case 2: case 3: case 6: case 7: case 8: return 3;
+        case 4: return 5;
+        case 5: return 2;
         default: return 0;
     }
 }
@@ -1426,13 +1294,14 @@ int sun_rows_per_lane(int nc, int v) {
     if (v < 0) v = 0;
     if (v >= sun_variant_count(nc)) return 0;
     const int code = sun_code(nc, v);
-    return code == kLds ? 1 : code;
+    return code >= kLds ? 1 : code;
 }
 
 int sun_variant_lds(int nc, int v) {
     if (v < 0) v = 0;
     if (v >= sun_variant_count(nc)) return -1;
-    return sun_code(nc, v) == kLds ? 1 : 0;
+    const int code = sun_code(nc, v);
+    return code == kLds ? 1 : (code == kMx ? 2 : 0);
 }
 
 // links (sites) a wave holds: R rows per lane, or the LDS-operand variant's one
@@ -1496,6 +1365,7 @@ hipError_t launch_stage_sun(int nc, int variant, hipStream_t s, const CfgDesc *c
     if (n_tiles <= 0) return hipSuccess;
     if (variant >= sun_variant_count(nc)) return hipErrorInvalidValue;
     const SunStageArgs a{cfgs, tile_start, n_act, n_tiles, step, stage, eps};
+    if (sun_code(nc, variant < 0 ? 0 : variant) == kMx) return launch_stage_sun_mfma(nc, s, a);
     TGF_SUN_DISPATCH(stage_nr, s, a)
 }
 
@@ -1504,6 +1374,9 @@ hipError_t launch_measure_sun(int nc, int variant, hipStream_t s, const CfgDesc 
                               double *partials, int buf_sel) {
     if (n_tiles <= 0) return hipSuccess;
     if (variant >= sun_variant_count(nc)) return hipErrorInvalidValue;
+    if (sun_code(nc, variant < 0 ? 0 : variant) == kMx)
+        return launch_measure_sun_mfma(nc, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials,
+                                       buf_sel);
     TGF_SUN_DISPATCH(measure_nr, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel)
 }
 
@@ -1511,6 +1384,12 @@ hipError_t launch_measure_sun(int nc, int variant, hipStream_t s, const CfgDesc 
 
 hipError_t launch_pack_sun(int nc, hipStream_t s, const void *src, void *W, int V, int stride) {
     const int nn = nc * nc;
+    if (sun_aos(nc)) {
+        const size_t n = (size_t)V * 4 * nn;
+        hipLaunchKernelGGL(sun_pack_aos_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           (const double2 *)src, (double2 *)W, n, stride, nn);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(sun_pack_kernel, dim3((V + 255) / 256, 4 * nn), dim3(256), 0, s,
                        (const double2 *)src, (double2 *)W, V, stride, nn);
     return hipGetLastError();
@@ -1518,6 +1397,12 @@ hipError_t launch_pack_sun(int nc, hipStream_t s, const void *src, void *W, int 
 
 hipError_t launch_unpack_sun(int nc, hipStream_t s, const void *W, void *dst, int V, int stride) {
     const int nn = nc * nc;
+    if (sun_aos(nc)) {
+        const size_t n = (size_t)V * 4 * nn;
+        hipLaunchKernelGGL(sun_unpack_aos_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           (const double2 *)W, (double2 *)dst, n, stride, nn);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(sun_unpack_kernel, dim3((V + 255) / 256, 4 * nn), dim3(256), 0, s,
                        (const double2 *)W, (double2 *)dst, V, stride, nn);
     return hipGetLastError();
