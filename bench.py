@@ -101,7 +101,7 @@ def flops_per_site_stage(storage, variant):
     """Real FP operations per site for one RK stage, by kernel."""
     c12 = storage == "f32c12"
     upd = R2 if c12 else MM
-    if variant.startswith(("site_alg", "site_lds", "site_plq")):
+    if variant.startswith(("site_alg", "site_lds", "site_plq", "quad")):
         if storage == "f64":
             # six two-row plaquettes projected to su(3) (r2_proj_ah ~55, +-accumulate 16),
             # twelve lower staples (a product and an accumulated product, 2 MM + 18),
@@ -620,6 +620,8 @@ def block_shapes(f, cfgs):
 def kernel_name(variant, storage):
     if variant.startswith("site_alg3"):
         kname = "stage_site_alg3_kernel"
+    elif variant.startswith("quad"):
+        kname = "stage_quad_kernel"
     elif variant.startswith("site_lds"):
         kname = "stage_site_lds_kernel"
     elif variant.startswith("site_plq"):

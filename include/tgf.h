@@ -244,8 +244,8 @@ tgf_status tgf_unitarity(tgf_ctx *c, int32_t cfg, double *out);
 /* Tune the stage kernel on the loaded links (stage 0 timed with HIP events,
  * links restored afterwards; the batched ensemble of the paper's Table A.1
  * mixes extents, so shapes are tuned per extent):
- *   (1) the variant, timed on the whole batch, among the XCD-ordered site and
- *       link kernels (the LDS-staged one first); a candidate replaces the
+ *   (1) the variant, timed on the whole batch, among the XCD-ordered quad, site
+ *       and link kernels (the quad one first); a candidate replaces the
  *       current choice only when it is more than 2% faster;
  *   (2) for the LDS-staged variants, the work-group shape of each class of
  *       configurations with equal extents: whole (n0, n1) planes (the
@@ -267,7 +267,7 @@ tgf_status tgf_get_block(tgf_ctx *c, int32_t cfg, int32_t *sites);
 tgf_status tgf_set_block(tgf_ctx *c, int32_t cfg, int32_t sites);
 
 /* Select a stage-kernel variant by index (0 .. tgf_variant_count()-1), or
- * -1 for the built-in default ("site_lds_xcd", the LDS-staged site kernel;
+ * -1 for the built-in default ("quad_xcd", one wave per direction and tile;
  * general SU(N) contexts: variant 0). */
 tgf_status tgf_set_variant(tgf_ctx *c, int32_t variant);
 int32_t tgf_get_variant(tgf_ctx *c);

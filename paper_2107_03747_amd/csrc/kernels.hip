@@ -21,6 +21,7 @@
 #include <float.h>
 #include <math.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "launch.h"
 #include "lattice_dev.h"
@@ -494,6 +495,275 @@ template <class R, int NE>
 __global__ __launch_bounds__(256, sizeof(R) == 8 ? 1 : (NE == 6 ? 3 : 2))
 void stage_site_lds_kernel(StageArgs a) {
     site_lds_body<R, NE>(a);
+}
+
+// ---------------------------------------------------------------------------
+// Quad variant: a work-group is one tile of 64 consecutive sites of a
+// configuration, one wave per link direction.  The eighteen closed loops of a
+// site (six upper plaquettes, twelve lower loops) are dealt to the four waves,
+// the raw forms of the upper plaquettes pass through LDS to both of their
+// links, and every wave updates its own link.  Where a tile is closed under
+// the shift by one site in direction 0 or 1 (whole rows, whole planes), the
+// lower loops of that direction are not formed: the wave that formed the
+// plaquette P_{mu nu}(n) conjugates its raw form by its own links,
+//   U_nu(n)^+ P U_nu(n) for link mu at n + nu,  U_mu(n)^+ P U_mu(n) for link nu
+// at n + mu, and the lanes of those sites take the results from LDS.
+// What a wave forms depends on its configuration's extents alone, so results
+// do not depend on the batch around it.
+//
+// Why, against one thread per site over 256-site blocks (stage_site_lds_kernel):
+//   - a site's chain of loops is a quarter as long and a small box fills four
+//     times the waves: 4x4x12x12 12-real 22.3 -> 9.0 us per stage, 6x6x18x18
+//     FP64 31.9 -> 14.3 us;
+//   - a wave holds one link's force (90 / 106 / 197 registers against 141 / 211 /
+//     490), so five, four and two waves share a SIMD instead of three, two and
+//     one: non-packed FP32 instructions of two waves issue together (2.1 cycles
+//     per instruction and SIMD with an even number of waves, 4.2 with one);
+//   - four waves read the same neighbours at about the same time: 1.16 instead
+//     of 1.98 GB past the L2 per launch on the 96-configuration batch.
+// Stage launch, 3.5e6 sites of 8x8x24x24, 10x10x30x30, 16x16x48x48 in turn:
+// 12-real 613 -> 590, 824 -> 770, 709 -> 700 us (12x12x36x36 1020 -> 800);
+// FP32 full 865 -> 700, 1020 -> 1005, 980 -> 900; FP64 1940 -> 1450, 2360 ->
+// 1990, 2725 -> 1785.  Under this load the clock falls to 1.4-1.6 GHz, so what
+// is left is energy: operations and bytes moved, not waves or latency.  Tried:
+// third rows of 12-real links kept in LDS (-6% instructions, 33 KB) +7%; six
+// waves per SIMD (own link re-read from LDS) +2%; links requested two or three
+// uses ahead +2% and +12% (registers).
+
+template <class R, int NE>
+struct QuadShape {
+    static constexpr int NU = sizeof(R) == 8 ? 9 : (NE == 6 ? 3 : 4);   // 16-byte units of a link
+    static constexpr int NA = 8 * (int)sizeof(R) / 16;                  // and of a raw form
+    static constexpr bool kE8 = sizeof(R) == 4 && NE == 9;              // entry 8 alone
+};
+
+template <class R>
+using QU16 = R __attribute__((ext_vector_type(16 / sizeof(R))));
+
+// The LDS of a tile: its links, the raw forms of its upper plaquettes (by
+// plane), and the one conjugated form that another wave needs (link 1 from
+// direction 0).
+template <class R, int NE>
+struct QuadLds {
+    typedef QuadShape<R, NE> Sh;
+    QU16<R> link[4 * Sh::NU * kTile];
+    QU16<R> raw[7 * Sh::NA * kTile];
+    v2<R> e8[Sh::kE8 ? 4 * kTile : 1];
+};
+
+template <class R>
+__device__ __forceinline__ void put_raw(QU16<R> *q, int slot, int k, const R r[8]) {
+    constexpr int NA = 8 * (int)sizeof(R) / 16, W = 16 / (int)sizeof(R);
+#pragma unroll
+    for (int u = 0; u < NA; u++) {
+        QU16<R> v;
+#pragma unroll
+        for (int x = 0; x < W; x++) v[x] = r[W * u + x];
+        q[(slot * NA + u) * kTile + k] = v;
+    }
+}
+// f += the raw form, or f -= it
+template <class R>
+__device__ __forceinline__ void add_raw(const QU16<R> *q, int slot, int k, bool neg, R f[8]) {
+    constexpr int NA = 8 * (int)sizeof(R) / 16, W = 16 / (int)sizeof(R);
+    const R sg = neg ? R(-1) : R(1);
+#pragma unroll
+    for (int u = 0; u < NA; u++) {
+        const QU16<R> v = q[(slot * NA + u) * kTile + k];
+#pragma unroll
+        for (int x = 0; x < W; x++) f[W * u + x] = fma(sg, v[x], f[W * u + x]);
+    }
+}
+
+// A lane's view of the links: its tile's in LDS, all in global memory.
+template <class R, int NE>
+struct QuadLinks {
+    typedef QuadShape<R, NE> Sh;
+    Links<R, NE> gl;
+    QuadLds<R, NE> *s;
+    int k;                        // this lane's slot in the tile
+    bool dn0, dn1, up0, up1;      // every lane finds n - 0, n - 1, n + 0, n + 1 in the tile
+    __device__ __forceinline__ void put(int mu, const M3<R> &U) const {
+        QU16<R> *q = s->link + mu * Sh::NU * kTile + k;
+        if constexpr (sizeof(R) == 4) {
+            q[0] = QU16<R>{U.e[0][0].x, U.e[0][0].y, U.e[0][1].x, U.e[0][1].y};
+            q[kTile] = QU16<R>{U.e[0][2].x, U.e[0][2].y, U.e[1][0].x, U.e[1][0].y};
+            q[2 * kTile] = QU16<R>{U.e[1][1].x, U.e[1][1].y, U.e[1][2].x, U.e[1][2].y};
+            if constexpr (Sh::kE8) {
+                q[3 * kTile] = QU16<R>{U.e[2][0].x, U.e[2][0].y, U.e[2][1].x, U.e[2][1].y};
+                s->e8[mu * kTile + k] = v2<R>{U.e[2][2].x, U.e[2][2].y};
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 9; e++) q[e * kTile] = QU16<R>{U.e[e / 3][e % 3].x, U.e[e / 3][e % 3].y};
+        }
+    }
+    __device__ __forceinline__ M3<R> tile(int mu, int at) const {
+        const QU16<R> *q = s->link + mu * Sh::NU * kTile + at;
+        M3<R> U;
+        if constexpr (sizeof(R) == 4) {
+            const QU16<R> a = q[0], b = q[kTile], c = q[2 * kTile];
+            U.e[0][0] = {a[0], a[1]};
+            U.e[0][1] = {a[2], a[3]};
+            U.e[0][2] = {b[0], b[1]};
+            U.e[1][0] = {b[2], b[3]};
+            U.e[1][1] = {c[0], c[1]};
+            U.e[1][2] = {c[2], c[3]};
+            if constexpr (Sh::kE8) {
+                const QU16<R> d = q[3 * kTile];
+                const v2<R> z = s->e8[mu * kTile + at];
+                U.e[2][0] = {d[0], d[1]};
+                U.e[2][1] = {d[2], d[3]};
+                U.e[2][2] = {z.x, z.y};
+            } else {
+                rebuild_row2(U);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 9; e++) {
+                const QU16<R> v = q[e * kTile];
+                U.e[e / 3][e % 3] = {v[0], v[1]};
+            }
+        }
+        return U;
+    }
+    __device__ __forceinline__ M3<R> own(int mu) const { return tile(mu, k); }
+    __device__ __forceinline__ M3<R> up(int nu, int mu, const Geo &g) const {   // U_nu(n + mu)
+        if ((mu == 0 && up0) || (mu == 1 && up1)) return tile(nu, k + g.up(mu));
+        return gl(nu, g.i + g.up(mu));
+    }
+};
+
+// Raw form of the upper plaquette of plane (A, B) at n.
+template <class R, int NE, int A, int B>
+__device__ __forceinline__ void quad_plane(const QuadLinks<R, NE> &W, const CfgDesc &c,
+                                           const Geo &g, R r[8]) {
+    R2<R> P = r2_of(W.own(A));
+    P = r2_mul_nn(P, W.up(B, A, g));
+    P = r2_mul_nd(P, W.up(A, B, g));
+    P = r2_mul_nd(P, W.own(B));
+    const int k = c.tw[plane_index(A, B)];
+    if (k && g.n(A) == 0 && g.n(B) == 0) r2_scale(P, cconj(omega_pow<R>(k)));
+    r2_raw(P, r);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The term of this wave's own link at n + dir: r conjugated by U_dir(n), through
+// the plane's slot (which r takes afterwards; a wave's LDS accesses are carried
+// out in order) to the lane of that site.
+template <class R, int NE>
+__device__ __forceinline__ void quad_pass(const QuadLinks<R, NE> &W, const Geo &g, const R r[8],
+                                          int dir, int slot, bool neg, R f[8]) {
+    R t[8];
+    conj_raw(W.own(dir), r, t);
+    put_raw<R>(W.s->raw, slot, W.k, t);
+    __builtin_amdgcn_wave_barrier();
+    add_raw<R>(W.s->raw, slot, W.k + g.dn(dir), neg, f);
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The terms of the wave of direction MU: its planes -- wave 0 (0,1); 1 (2,3);
+// 2 (0,2), (1,2); 3 (0,3), (1,3) -- and the lower loops of link MU that the
+// tile does not give, U_mu(n) U_nu(n+mu-nu)^+ U_mu(n-nu)^+ U_nu(n-nu).
+template <class R, int NE, int MU>
+__device__ __forceinline__ void quad_terms(const QuadLinks<R, NE> &W, const CfgDesc &c,
+                                           const Geo &g, const M3<R> &own, R f[8]) {
+    R r[8];
+    if constexpr (MU == 0) {
+        quad_plane<R, NE, 0, 1>(W, c, g, r);
+        if (W.dn1) quad_pass<R, NE>(W, g, r, 1, 0, true, f);
+        if (W.dn0) {                          // for link 1 at n + 0: wave 1 takes it
+            R t[8];
+            conj_raw(W.own(0), r, t);
+            put_raw<R>(W.s->raw, 6, W.k, t);
+        }
+        put_raw<R>(W.s->raw, 0, W.k, r);
+    } else if constexpr (MU == 1) {
+        quad_plane<R, NE, 2, 3>(W, c, g, r);
+        put_raw<R>(W.s->raw, 5, W.k, r);
+    } else {
+        quad_plane<R, NE, 0, MU>(W, c, g, r);
+        if (W.dn0) quad_pass<R, NE>(W, g, r, 0, MU - 1, false, f);
+        put_raw<R>(W.s->raw, MU - 1, W.k, r);
+        quad_plane<R, NE, 1, MU>(W, c, g, r);
+        if (W.dn1) quad_pass<R, NE>(W, g, r, 1, MU + 1, false, f);
+        put_raw<R>(W.s->raw, MU + 1, W.k, r);
+    }
+#pragma unroll
+    for (int nu = 0; nu < 4; nu++) {
+        if (nu == MU || (nu == 0 && W.dn0) || (nu == 1 && W.dn1)) continue;
+        __builtin_amdgcn_sched_barrier(0);
+        const int j = g.i + g.dn(nu);
+        R2<R> P = r2_of(own);
+        P = r2_mul_nd(P, W.gl(nu, j + g.up(MU)));
+        P = r2_mul_nd(P, W.gl(MU, j));
+        P = r2_mul_nn(P, W.gl(nu, j));
+        const int k = twist_exp(c, MU, nu);
+        if (k && g.n(MU) == 0 && g.back(nu) == 0) r2_scale(P, omega_pow<R>(k));
+        r2_raw(P, r);
+#pragma unroll
+        for (int t = 0; t < 8; t++) f[t] += r[t];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <class R>
+struct OwnLink {   // the link a wave updates, held in registers throughout
+    M3<R> U;
+    __device__ __forceinline__ M3<R> own(int, int) const { return U; }
+};
+
+template <class R, int NE>
+__global__ __launch_bounds__(256, sizeof(R) == 8 ? 2 : (NE == 9 ? 4 : 5))
+void stage_quad_kernel(StageArgs a) {
+    __shared__ QuadLds<R, NE> s;
+    const int b = remap_block(blockIdx.x, a.n_tiles, a.xcd);
+    if (b >= a.n_tiles) return;                            // whole work-group
+    const int ci = find_cfg(a.tile_start, a.n_act, b);
+    const CfgDesc c = a.cfgs[ci];
+    const int tb = (b - a.tile_start[ci]) * kTile;
+    const int nw = min(kTile, c.V - tb);
+    const int lane = threadIdx.x & 63;
+    const bool live = lane < nw;
+    const int i = tb + (live ? lane : nw - 1);   // idle lanes repeat the last site, slot and all
+    // the wave of a direction changes from tile to tile: the directions' work
+    // differs by a tenth, and a work-group's waves go to the four SIMDs in order
+    const int mu = __builtin_amdgcn_readfirstlane(((threadIdx.x >> 6) + b) & 3);
+
+    const int in = (c.cur + 3 * a.step + a.stage) & 1;
+    QuadLinks<R, NE> W{Links<R, NE>{as_global<R>((const void *)(in ? c.W[1] : c.W[0])), c.stride},
+                       &s, i - tb, false, false, false, false};
+    const OwnLink<R> O{W.gl(mu, i)};
+    W.put(mu, O.U);
+    const Geo g = make_geo_inv(c, i);
+    W.dn0 = __all((unsigned)(i + g.dn(0) - tb) < (unsigned)nw);
+    W.dn1 = __all((unsigned)(i + g.dn(1) - tb) < (unsigned)nw);
+    W.up0 = __all((unsigned)(i + g.up(0) - tb) < (unsigned)nw);
+    W.up1 = __all((unsigned)(i + g.up(1) - tb) < (unsigned)nw);
+    __syncthreads();
+
+    R f[8];
+#pragma unroll
+    for (int t = 0; t < 8; t++) f[t] = R(0);
+    switch (mu) {
+        case 0: quad_terms<R, NE, 0>(W, c, g, O.U, f); break;
+        case 1: quad_terms<R, NE, 1>(W, c, g, O.U, f); break;
+        case 2: quad_terms<R, NE, 2>(W, c, g, O.U, f); break;
+        default: quad_terms<R, NE, 3>(W, c, g, O.U, f); break;
+    }
+    __syncthreads();
+    if (!live) return;
+    // the upper plaquettes of the link, and link 1's term from n - 0
+#pragma unroll
+    for (int d = 0; d < 4; d++)
+        if (d != mu)
+            add_raw<R>(s.raw, mu < d ? plane_index(mu, d) : plane_index(d, mu), lane, mu > d, f);
+    if (mu == 1 && W.dn0) add_raw<R>(s.raw, 6, lane + g.dn(0), false, f);
+    const double eps = a.step < c.n_full ? a.eps : c.eps_last;
+    const R beps = (R)(kRkB[a.stage] * eps);
+    const R ac = (R)kRkA[a.stage];
+    update_link_z<R, NE>(O, as_global<R>(in ? c.W[0] : c.W[1]), as_global<R>(c.X), c.stride, mu, i,
+                         raw_to_alg(f, -beps), ac, a.stage, reunit_now(a, c));
 }
 
 // Lower staple terms of link MU (from the block's plaquettes in LDS where the
@@ -1058,6 +1328,8 @@ const char *variant_name(int v) {
         case V_SITE_LDS_XCD: return "site_lds_xcd";
         case V_SITE_PLQ: return "site_plq";
         case V_SITE_PLQ_XCD: return "site_plq_xcd";
+        case V_QUAD: return "quad";
+        case V_QUAD_XCD: return "quad_xcd";
         default: return "?";
     }
 }
@@ -1065,7 +1337,7 @@ const char *variant_name(int v) {
 template <class R, int NE>
 static hipError_t launch_stage_t(int variant, hipStream_t s, const StageArgs &a) {
     const bool xcd = variant == V_SITE_XCD || variant == V_LINK_XCD || variant == V_SITE_ALG_XCD || variant == V_SITE_ALG3_XCD ||
-                     variant == V_SITE_LDS_XCD || variant == V_SITE_PLQ_XCD;
+                     variant == V_SITE_LDS_XCD || variant == V_SITE_PLQ_XCD || variant == V_QUAD_XCD;
     StageArgs b = a;
     b.xcd = xcd ? 1 : 0;
     const int site_blocks = xcd ? ((a.n_tiles + 3) / 4 + 7) / 8 * 8 : (a.n_tiles + 3) / 4;
@@ -1087,6 +1359,8 @@ static hipError_t launch_stage_t(int variant, hipStream_t s, const StageArgs &a)
                                b);
     } else if (variant == V_SITE_PLQ || variant == V_SITE_PLQ_XCD) {
         hipLaunchKernelGGL((stage_site_plq_kernel<R, NE>), dim3(site_blocks), dim3(256), 0, s, b);
+    } else if (variant == V_QUAD || variant == V_QUAD_XCD) {
+        hipLaunchKernelGGL((stage_quad_kernel<R, NE>), dim3(tile_blocks), dim3(256), 0, s, b);
     } else {
         hipLaunchKernelGGL((stage_link_kernel<R, NE>), dim3(tile_blocks), dim3(256), 0, s, b);
     }

@@ -28,7 +28,10 @@ enum Variant {
     V_SITE_PLQ = 10,  // V_SITE_ALG with the block's upper plaquettes kept in LDS and
                       // reused, conjugated, as in-block lower staple terms
     V_SITE_PLQ_XCD = 11,
-    V_COUNT = 12
+    V_QUAD = 12,      // a work-group per 64-site tile, one wave per direction, the
+                      // site's loops dealt to the waves and shared through LDS
+    V_QUAD_XCD = 13,  // the default
+    V_COUNT = 14
 };
 const char *variant_name(int v);
 

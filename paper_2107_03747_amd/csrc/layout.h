@@ -44,6 +44,7 @@ struct CfgDesc {
     int32_t chunk;        // their launch order: 0 = site order, else columns of chunk blocks
     double eps_last;      // size of the short final step (0 if none)
     double t0;            // flow time at the start of this flow
+    double inv[3];        // 1 / d[0..2] (make_geo_inv)
     void *W[2];
     void *X;
 };

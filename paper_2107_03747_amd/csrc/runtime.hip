@@ -240,7 +240,7 @@ struct tgf_ctx {
     int effective_variant() const {
         if (general) return variant >= 0 ? variant : 0;
         if (variant >= 0) return variant;
-        return V_SITE_LDS_XCD;   // the fastest measured for all three storages
+        return V_QUAD_XCD;   // the fastest measured for all three storages
     }
 };
 
@@ -266,6 +266,7 @@ void fill_desc(const tgf_ctx *c, const CfgHost &h, int user, CfgDesc &d) {
     d.user = user;
     d.cur = h.cur;
     d.t0 = h.t;
+    for (int m = 0; m < 3; m++) d.inv[m] = 1.0 / h.d[m];
     d.blk = h.blk;
     d.chunk = block_chunk(h.d, h.blk);
     d.W[0] = c->ws + h.offW[0];
@@ -1139,7 +1140,7 @@ tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path) {
         if (c->general)
             for (int v = 0; v < c->variant_count(); v++) cand.push_back(v);
         else
-            cand = {V_SITE_LDS_XCD, V_SITE_ALG_XCD, V_SITE_ALG3_XCD, V_SITE_XCD, V_LINK_XCD};
+            cand = {V_QUAD_XCD, V_SITE_LDS_XCD, V_SITE_ALG_XCD, V_SITE_ALG3_XCD, V_SITE_XCD, V_LINK_XCD};
         float best_ms = 0;
         for (size_t j = 0; j < cand.size(); j++) {
             float ms = 0;

@@ -359,50 +359,52 @@ __device__ __forceinline__ Alg<R> raw_to_alg(const R k[8], R s) {
 
 // Raw form of U^+ M U from the raw form k of M: with T the traceless part of
 // M - M^+ (off-diagonals z_ij, diagonal 2i (2u - v)/3, 2i (2v - u)/3, ...),
-// B = T U, C = U^+ B (upper off-diagonals and the first two diagonal entries;
-// C is traceless, so Im C_22 = -(Im C_00 + Im C_11)).
+// B = T U, C = U^+ B.  Only the upper off-diagonals and the last two diagonal
+// entries of C are formed (C is traceless), for which columns 1 and 2 of B
+// are enough.
 template <class R>
 __device__ __forceinline__ void conj_raw(const M3<R> &U, const R k[8], R c[8]) {
     const cx<R> x01 = {k[0], k[1]}, x02 = {k[2], k[3]}, x12 = {k[4], k[5]};
     const R w = R(2.0 / 3.0);
     const R d0 = w * fma(R(2), k[6], -k[7]), d1 = w * fma(R(2), k[7], -k[6]);
     const R d2 = -(d0 + d1);
-    M3<R> B;
+    cx<R> B[3][2];   // columns 1, 2
 #pragma unroll
-    for (int j = 0; j < 3; j++) {
-        cx<R> t = {-d0 * U.e[0][j].y, d0 * U.e[0][j].x};
-        t = cmadd(t, x01, U.e[1][j]);
-        t = cmadd(t, x02, U.e[2][j]);
-        B.e[0][j] = t;
-        t = {-d1 * U.e[1][j].y, d1 * U.e[1][j].x};
-        t = cmadd(t, cx<R>{-x01.x, x01.y}, U.e[0][j]);
-        t = cmadd(t, x12, U.e[2][j]);
-        B.e[1][j] = t;
-        t = {-d2 * U.e[2][j].y, d2 * U.e[2][j].x};
-        t = cmadd(t, cx<R>{-x02.x, x02.y}, U.e[0][j]);
-        t = cmadd(t, cx<R>{-x12.x, x12.y}, U.e[1][j]);
-        B.e[2][j] = t;
+    for (int j = 0; j < 2; j++) {
+        const cx<R> u0 = U.e[0][j + 1], u1 = U.e[1][j + 1], u2 = U.e[2][j + 1];
+        cx<R> t = {-d0 * u0.y, d0 * u0.x};
+        t = cmadd(t, x01, u1);
+        t = cmadd(t, x02, u2);
+        B[0][j] = t;
+        t = {-d1 * u1.y, d1 * u1.x};
+        t = cmadd(t, cx<R>{-x01.x, x01.y}, u0);
+        t = cmadd(t, x12, u2);
+        B[1][j] = t;
+        t = {-d2 * u2.y, d2 * u2.x};
+        t = cmadd(t, cx<R>{-x02.x, x02.y}, u0);
+        t = cmadd(t, cx<R>{-x12.x, x12.y}, u1);
+        B[2][j] = t;
     }
-    const int ia[3] = {0, 0, 1}, ib[3] = {1, 2, 2};
+    const int ia[3] = {0, 0, 1}, ib[3] = {0, 1, 1};   // C_01, C_02, C_12
 #pragma unroll
     for (int t = 0; t < 3; t++) {
         cx<R> s = {R(0), R(0)};
 #pragma unroll
-        for (int m = 0; m < 3; m++) s = cmadd_cn(s, U.e[m][ia[t]], B.e[m][ib[t]]);
+        for (int m = 0; m < 3; m++) s = cmadd_cn(s, U.e[m][ia[t]], B[m][ib[t]]);
         c[2 * t] = s.x;
         c[2 * t + 1] = s.y;
     }
-    R im[2];
+    R im[2];   // Im C_11, Im C_22
 #pragma unroll
     for (int d = 0; d < 2; d++) {
         R v = 0;
 #pragma unroll
-        for (int m = 0; m < 3; m++) v = fma(U.e[m][d].x, B.e[m][d].y, fma(-U.e[m][d].y, B.e[m][d].x, v));
+        for (int m = 0; m < 3; m++) v = fma(U.e[m][d + 1].x, B[m][d].y, fma(-U.e[m][d + 1].y, B[m][d].x, v));
         im[d] = v;
     }
-    // u' = (Im C00 - Im C22)/2 = Im C00 + Im C11 / 2, v' = Im C11 + Im C00 / 2
-    c[6] = fma(R(0.5), im[1], im[0]);
-    c[7] = fma(R(0.5), im[0], im[1]);
+    // u' = (Im C00 - Im C22)/2 = -Im C11 / 2 - Im C22, v' = (Im C11 - Im C22)/2
+    c[6] = fma(R(-0.5), im[0], -im[1]);
+    c[7] = R(0.5) * (im[0] - im[1]);
 }
 
 // C = U^+ A U for A in su(3) (8-real form); the result is again in su(3).
