@@ -721,7 +721,7 @@ void stage_quad_kernel(StageArgs a) {
     if (b >= a.n_tiles) return;                            // whole work-group
     const int ci = find_cfg(a.tile_start, a.n_act, b);
     const CfgDesc c = a.cfgs[ci];
-    const int tb = (b - a.tile_start[ci]) * kTile;
+    const int tb = tile_order(b - a.tile_start[ci], c) * kTile;
     const int nw = min(kTile, c.V - tb);
     const int lane = threadIdx.x & 63;
     const bool live = lane < nw;

@@ -211,13 +211,20 @@ __host__ __device__ __forceinline__ int find_cfg(const int *__restrict__ tile_st
 // (along n2) and each column is walked through all n3 before the next: the
 // direction-3 neighbours are c.chunk blocks away.  A one-to-one map of
 // 0 .. V/blk - 1; needs d0 d1 d2 to be a multiple of blk * c.chunk.
-__host__ __device__ __forceinline__ int block_order(int j, const CfgDesc &c) {
-    if (!c.chunk) return j;
-    const int slice = c.d[0] * c.d[1] * c.d[2] / c.blk;   // blocks per n3 slice
-    const int col = c.chunk * c.d[3];                     // blocks per column
+__host__ __device__ __forceinline__ int column_order(int j, const CfgDesc &c, int blk, int chunk) {
+    if (!chunk) return j;
+    const int slice = c.d[0] * c.d[1] * c.d[2] / blk;     // blocks per n3 slice
+    const int col = chunk * c.d[3];                       // blocks per column
     const int k = j / col, r = j - k * col;
-    const int n3 = r / c.chunk;
-    return n3 * slice + k * c.chunk + (r - n3 * c.chunk);
+    const int n3 = r / chunk;
+    return n3 * slice + k * chunk + (r - n3 * chunk);
+}
+__host__ __device__ __forceinline__ int block_order(int j, const CfgDesc &c) {
+    return column_order(j, c, c.blk, c.chunk);
+}
+// the same for 64-site tiles (the quad variant)
+__host__ __device__ __forceinline__ int tile_order(int j, const CfgDesc &c) {
+    return column_order(j, c, kTile, c.tchunk);
 }
 
 // A wave-uniform pointer taken through readfirstlane: the result is known to

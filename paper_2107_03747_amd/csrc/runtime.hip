@@ -110,6 +110,25 @@ int block_chunk(const int d[4], int blk) {
     return 0;
 }
 
+// Column width of the quad variant's 64-site tiles (tile_order): site order
+// while an n3 slice spans at most kTileSlice tiles (about what an XCD runs at a
+// time), else four (n0, n1) planes, or the largest divisor of the slice's tile
+// count below that.  Stage launch, site order against columns of 2 / 4 / 8
+// planes (us, 12-real, FP32 full, FP64): 32x32x96x96 1982, 2891, 6669 against
+// 1913, 2695, 6434 / 1850, 2626, 6331 / 1867, 2656, 6298; 16x16x48x48 x 6 (192
+// tiles per slice) 700, 892, 1775 against, for 4 / 8 / 16 planes, 687, 843,
+// 1668 / 690, 849, 1687 / 697, 873, 1734.
+constexpr int kTileSlice = 128;
+int tile_chunk(const int d[4]) {
+    const long long s = (long long)d[0] * d[1] * d[2];
+    if (s % 64) return 0;
+    const long long slice = s / 64, planes = std::max(16LL, 4LL * d[0] * d[1] / 64);
+    if (slice <= kTileSlice) return 0;
+    for (long long ch = std::min(planes, slice); ch >= 8; ch--)
+        if (slice % ch == 0) return (int)ch;
+    return 0;
+}
+
 // The other candidate the autotuner times for a configuration (0 if none).
 int other_block(const int d[4]) {
     const int b = default_block(d);
@@ -269,6 +288,7 @@ void fill_desc(const tgf_ctx *c, const CfgHost &h, int user, CfgDesc &d) {
     for (int m = 0; m < 3; m++) d.inv[m] = 1.0 / h.d[m];
     d.blk = h.blk;
     d.chunk = block_chunk(h.d, h.blk);
+    d.tchunk = tile_chunk(h.d);
     d.W[0] = c->ws + h.offW[0];
     d.W[1] = c->ws + h.offW[1];
     d.X = c->ws + h.offX;

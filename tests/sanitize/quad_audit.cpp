@@ -5,6 +5,7 @@
 //    coordinates: on every site of small boxes, and on the sites around every
 //    multiple of each divisor's block near the ends and at random of boxes up
 //    to the site cap (2^28 - 256).
+//  - The column order of a large box's tiles is a one-to-one map.
 //  - Every tile of 64 sites: where all lanes find n - 0, n - 1, n + 0 or n + 1
 //    in the tile, those are slots of the tile that hold that site; the sites
 //    of the lanes past the end are the last one; and a wave's lanes that take a
@@ -77,7 +78,24 @@ static void tiles(const CfgDesc &c) {
     }
 }
 
+static void columns(std::array<int, 4> d, int chunk) {
+    CfgDesc c = desc(d);
+    c.tchunk = chunk;
+    const int n = (c.V + kTile - 1) / kTile;
+    std::vector<int> seen(n, 0);
+    for (int j = 0; j < n; j++) {
+        checked++;
+        const int t = tile_order(j, c);
+        if (t < 0 || t >= n || seen[t]++) fail("tile order", c, j);
+    }
+}
+
 int main() {
+    columns({16, 16, 48, 48}, 16);
+    columns({32, 32, 96, 12}, 64);
+    columns({20, 20, 60, 5}, 25);
+    columns({24, 24, 72, 3}, 36);
+    columns({8, 8, 24, 24}, 0);
     const std::vector<std::array<int, 4>> small = {
         {2, 2, 2, 2}, {4, 4, 12, 12}, {3, 5, 4, 7}, {8, 8, 24, 24}, {6, 6, 18, 18}, {10, 10, 6, 6},
         {7, 7, 21, 5}, {9, 9, 9, 9}, {16, 16, 8, 4}, {64, 2, 2, 2}, {2, 32, 3, 2}, {65, 3, 2, 2},
