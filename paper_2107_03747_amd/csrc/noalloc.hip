@@ -73,7 +73,7 @@ __global__ __launch_bounds__(192) void measure_canon_kernel(CfgDesc c, const dou
 
 // One work-group: the fixed-order sum of the n_tiles x 3 partials, written as
 // one tgf_obs {t, E, t^2 E, plaq, Q, action} to out.
-__global__ __launch_bounds__(256) void finalize_canon_kernel(int V, int n_tiles, double t,
+__global__ __launch_bounds__(kSumThreads) void finalize_canon_kernel(int V, int n_tiles, double t,
                                                              const double *partials,
                                                              double *out) {
     double tot[4];
@@ -152,7 +152,7 @@ extern "C" tgf_status tgf_measure_noalloc(const tgf_geom *geom, const void *link
                        (const double2 *)links_dev, part);
     e = hipGetLastError();
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(finalize_canon_kernel, dim3(1), dim3(256), 0, s, (int)V, n_tiles, t,
+        hipLaunchKernelGGL(finalize_canon_kernel, dim3(1), dim3(kSumThreads), 0, s, (int)V, n_tiles, t,
                            (const double *)part, (double *)out_dev);
         e = hipGetLastError();
     }
