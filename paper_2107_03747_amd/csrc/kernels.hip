@@ -993,7 +993,7 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
     if (i < c.V) {
         const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
         const Links<R, NE> W{as_global<R>((const void *)(sel ? c.W[1] : c.W[0])), c.stride};
-        const Geo g = make_geo(c, i);
+        const Geo g = make_geo_inv(c, i);
         const int nw = min(kTile, c.V - tb);
         switch (pair) {
             case 0: measure_pair<R, 0>(W, c, g, v, tb, nw); break;
@@ -1010,15 +1010,54 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Topological charge per slice: q(s) = (1/16 pi^2) sum_{n : n_dir = s} Tr G G~
-// (eq. qlatt restricted to one slice).  Block (b, s) takes the sites
-// 256 b .. 256 b + 255 of slice s, one per thread; the sites of a slice are
-// enumerated over the three other directions in increasing order.  FP64
-// partials, summed in a fixed order.
+// Per-site densities of configuration ci: e(n) = sum_{mu<nu} Tr G^2 and
+// q(n) = (1/16 pi^2) Tr G G~, written to FP64 arrays in site order (either may
+// be null).  As the measurement: a work-group is one tile, one wave per dual
+// plane pair, leaves taken from the wave where it holds the neighbour; the
+// three pairs meet in LDS.  to_x: q(n) goes to the configuration's accumulator
+// buffer, which a flow writes before it reads it, for the slice sums below.
 template <class R, int NE>
-__global__ __launch_bounds__(256) void slice_charge_kernel(const CfgDesc *__restrict__ cfgs, int ci,
-                                                           int dir, double *__restrict__ partials) {
+__global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict__ cfgs, int ci,
+                                                      double *__restrict__ e_out,
+                                                      double *__restrict__ q_out, int to_x) {
+    const CfgDesc c = cfgs[ci];
+    if (to_x) q_out = (double *)c.X;
+    const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int tb = blockIdx.x * kTile, i = tb + lane;
+    __shared__ double part[2][2][kTile];
+    double v[4] = {0, 0, 0, 0};
+    if (i < c.V) {
+        const Links<R, NE> W{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride};
+        const Geo g = make_geo_inv(c, i);
+        const int nw = min(kTile, c.V - tb);
+        switch (pair) {
+            case 0: measure_pair<R, 0>(W, c, g, v, tb, nw); break;
+            case 1: measure_pair<R, 1>(W, c, g, v, tb, nw); break;
+            default: measure_pair<R, 2>(W, c, g, v, tb, nw); break;
+        }
+    }
+    if (pair) {
+        part[pair - 1][0][lane] = v[0];
+        part[pair - 1][1][lane] = v[1];
+    }
+    __syncthreads();
+    if (pair || i >= c.V) return;
+    if (e_out) e_out[i] = (v[0] + part[0][0][lane]) + part[1][0][lane];
+    if (q_out) q_out[i] = (v[1] + part[0][1][lane]) + part[1][1][lane];
+}
+
+// Topological charge per slice: q(s) = (1/16 pi^2) sum_{n : n_dir = s} Tr G G~
+// (eq. qlatt restricted to one slice), from the site densities that
+// density_kernel left in the accumulator buffer.  Block (b, s) sums the sites
+// 256 b .. 256 b + 255 of slice s, enumerated over the three other directions
+// in increasing order.  FP64 partials, summed in a fixed order.  (One thread
+// per site forming all six clovers of its site link by link, lanes of a slice
+// not being neighbours, took 594 us on 16x16x48x48 FP64; the densities take
+// half of that and the sums 10.)
+__global__ __launch_bounds__(256) void slice_sum_kernel(const CfgDesc *__restrict__ cfgs, int ci,
+                                                        int dir, double *__restrict__ partials) {
     const CfgDesc &c = cfgs[ci];   // read in place (c.d is indexed at run time)
+    const double *__restrict__ q = (const double *)c.X;
     const int s = blockIdx.y;
     const int S = c.V / c.d[dir];
     // the other three directions, increasing
@@ -1029,48 +1068,20 @@ __global__ __launch_bounds__(256) void slice_charge_kernel(const CfgDesc *__rest
     auto stride_of = [&](int m) {
         return m == 0 ? 1 : m == 1 ? c.d[0] : m == 2 ? c.d[0] * c.d[1] : c.d[0] * c.d[1] * c.d[2];
     };
-    double q = 0;
+    double t = 0;
     const int j = blockIdx.x * 256 + (int)threadIdx.x;
     if (j < S) {
         const int da = c.d[o0], db = c.d[o1];
         const int na = j % da, r = j / da;
         const int nb = r % db, nc = r / db;
-        const int i = na * stride_of(o0) + nb * stride_of(o1) + nc * stride_of(o2) + s * stride_of(dir);
-        const Links<R, NE> W{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride};
-        const Geo g = make_geo(c, i);
-        double v0[4], v1[4], v2[4];   // lanes do not hold consecutive sites: leaves formed link by link
-        measure_pair<R, 0>(W, c, g, v0);
-        measure_pair<R, 1>(W, c, g, v1);
-        measure_pair<R, 2>(W, c, g, v2);
-        q = (v0[1] + v1[1]) + v2[1];
+        t = q[na * stride_of(o0) + nb * stride_of(o1) + nc * stride_of(o2) + s * stride_of(dir)];
     }
-    q = wave_sum(q);
+    t = wave_sum(t);
     __shared__ double red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = q;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
     __syncthreads();
     if (threadIdx.x == 0)
         partials[(size_t)s * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// Per-site densities of configuration ci: e(n) = sum_{mu<nu} Tr G^2 and
-// q(n) = (1/16 pi^2) Tr G G~, from the three dual plane pairs, written to
-// FP64 arrays in site order (either may be null).
-template <class R, int NE>
-__global__ __launch_bounds__(256) void density_kernel(const CfgDesc *__restrict__ cfgs, int ci,
-                                                      double *__restrict__ e_out,
-                                                      double *__restrict__ q_out) {
-    const CfgDesc c = cfgs[ci];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= c.V) return;
-    const Links<R, NE> W{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride};
-    const Geo g = make_geo(c, i);
-    const int tb = i - (int)(threadIdx.x & 63), nw = min(64, c.V - tb);   // lanes = sites tb ..
-    double v0[4], v1[4], v2[4];
-    measure_pair<R, 0>(W, c, g, v0, tb, nw);
-    measure_pair<R, 1>(W, c, g, v1, tb, nw);
-    measure_pair<R, 2>(W, c, g, v2, tb, nw);
-    if (e_out) e_out[i] = (v0[0] + v1[0]) + v2[0];
-    if (q_out) q_out[i] = (v0[1] + v1[1]) + v2[1];
 }
 
 __global__ void slice_finalize_kernel(const double *__restrict__ partials, int n_slices, int chunks,
@@ -1481,22 +1492,30 @@ hipError_t launch_check_final(hipStream_t s, const double *partials, int ntiles,
     return hipGetLastError();
 }
 
+static hipError_t densities(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs, int ci, int V,
+                            double *e_out, double *q_out, int to_x) {
+    const dim3 grid((V + kTile - 1) / kTile);
+    if (p == P_F64)
+        hipLaunchKernelGGL((density_kernel<double, 9>), grid, dim3(192), 0, s, cfgs, ci, e_out,
+                           q_out, to_x);
+    else if (c12)
+        hipLaunchKernelGGL((density_kernel<float, 6>), grid, dim3(192), 0, s, cfgs, ci, e_out,
+                           q_out, to_x);
+    else
+        hipLaunchKernelGGL((density_kernel<float, 9>), grid, dim3(192), 0, s, cfgs, ci, e_out,
+                           q_out, to_x);
+    return hipGetLastError();
+}
+
 hipError_t launch_slice_charge(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs, int ci,
                                int dir, int n_slices, int slice_sites, double *partials,
                                double *out) {
-    const int chunks = (slice_sites + 255) / 256;
-    dim3 grid(chunks, n_slices);
-    if (p == P_F64)
-        hipLaunchKernelGGL((slice_charge_kernel<double, 9>), grid, dim3(256), 0, s, cfgs, ci, dir,
-                           partials);
-    else if (c12)
-        hipLaunchKernelGGL((slice_charge_kernel<float, 6>), grid, dim3(256), 0, s, cfgs, ci, dir,
-                           partials);
-    else
-        hipLaunchKernelGGL((slice_charge_kernel<float, 9>), grid, dim3(256), 0, s, cfgs, ci, dir,
-                           partials);
-    hipError_t e = hipGetLastError();
+    hipError_t e = densities(p, c12, s, cfgs, ci, n_slices * slice_sites, nullptr, nullptr, 1);
     if (e != hipSuccess) return e;
+    const int chunks = (slice_sites + 255) / 256;
+    hipLaunchKernelGGL(slice_sum_kernel, dim3(chunks, n_slices), dim3(256), 0, s, cfgs, ci, dir,
+                       partials);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(slice_finalize_kernel, dim3((n_slices + 63) / 64), dim3(64), 0, s, partials,
                        n_slices, chunks, out);
     return hipGetLastError();
@@ -1504,17 +1523,7 @@ hipError_t launch_slice_charge(Prec p, bool c12, hipStream_t s, const CfgDesc *c
 
 hipError_t launch_densities(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs, int ci, int V,
                             double *e_out, double *q_out) {
-    dim3 grid((V + 255) / 256);
-    if (p == P_F64)
-        hipLaunchKernelGGL((density_kernel<double, 9>), grid, dim3(256), 0, s, cfgs, ci, e_out,
-                           q_out);
-    else if (c12)
-        hipLaunchKernelGGL((density_kernel<float, 6>), grid, dim3(256), 0, s, cfgs, ci, e_out,
-                           q_out);
-    else
-        hipLaunchKernelGGL((density_kernel<float, 9>), grid, dim3(256), 0, s, cfgs, ci, e_out,
-                           q_out);
-    return hipGetLastError();
+    return densities(p, c12, s, cfgs, ci, V, e_out, q_out, 0);
 }
 
 hipError_t launch_fill_int(hipStream_t s, int *dst, int n, int value) {

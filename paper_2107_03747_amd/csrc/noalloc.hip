@@ -32,40 +32,65 @@ constexpr size_t kScratchDoubles = (size_t)kNoallocMaxTiles * 3 * 4;   // [tile]
 // passed to kernels or copies.
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
-// Canonical caller links: complex128 [site][mu][3][3].
+// Canonical caller links: complex128 [site][mu][3][3].  A link is 144
+// contiguous bytes, so a load per lane and entry would touch 64 cache lines
+// each time.  The wave reads its 64 links together instead: load k of a lane
+// is entry (64 k + lane) mod 9 of link (64 k + lane) / 9, nine lanes per link,
+// and the entries change lanes through 9 KB of LDS that belong to the wave
+// (its LDS accesses are carried out in order; the fences keep the compiler to
+// it).  Every lane of the wave takes part in every access.
 struct CanonLinks {
-    const double2 *p;
+    const v2<double> *p;
+    v2<double> *buf;      // [64][9]
+    int lane;
+    static __device__ __forceinline__ void fence() {
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+    }
     __device__ __forceinline__ M3<double> operator()(int mu, int i) const {
-        const double2 *s = p + ((size_t)i * 4 + mu) * 9;
+        v2<double> t[9];
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+            const int x = 64 * k + lane, s = (x * 7282) >> 16;   // x / 9 for x < 576
+            const int site = __shfl(i, s);
+            t[k] = p[((size_t)site * 4 + mu) * 9 + (x - 9 * s)];
+        }
+        fence();
+#pragma unroll
+        for (int k = 0; k < 9; k++) buf[64 * k + lane] = t[k];
+        fence();
         M3<double> U;
 #pragma unroll
-        for (int e = 0; e < 9; e++) U.e[e / 3][e % 3] = {s[e].x, s[e].y};
+        for (int e = 0; e < 9; e++) {
+            const v2<double> z = buf[9 * lane + e];
+            U.e[e / 3][e % 3] = {z.x, z.y};
+        }
+        fence();
         return U;
     }
 };
 
 // One work-group per tile of 64 sites, one wave per dual plane pair; the
-// wave's FP64 sums go to partials[tile][pair][4] (as measure_kernel).
+// wave's FP64 sums go to partials[tile][pair][4] (as measure_kernel).  Lanes
+// past the last site repeat it and count nothing.
 __global__ __launch_bounds__(192) void measure_canon_kernel(CfgDesc c, const double2 *links,
                                                             double *partials) {
+    __shared__ v2<double> buf[3][64 * 9];
     const int tile = blockIdx.x;
-    const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int tb = tile * kTile;                               // site of lane 0
-    const int i = tb + (threadIdx.x & 63);
+    const int nw = min(kTile, c.V - tb);
     double v[4] = {0, 0, 0, 0};
-    if (i < c.V) {
-        const CanonLinks W{links};
-        const Geo g = make_geo(c, i);
-        const int nw = min(kTile, c.V - tb);
-        switch (pair) {
-            case 0: measure_pair<double, 0>(W, c, g, v, tb, nw); break;
-            case 1: measure_pair<double, 1>(W, c, g, v, tb, nw); break;
-            default: measure_pair<double, 2>(W, c, g, v, tb, nw); break;
-        }
+    const CanonLinks W{(const v2<double> *)links, buf[pair], lane};
+    const Geo g = make_geo_inv(c, tb + min(lane, nw - 1));
+    switch (pair) {
+        case 0: measure_pair<double, 0>(W, c, g, v, tb, nw); break;
+        case 1: measure_pair<double, 1>(W, c, g, v, tb, nw); break;
+        default: measure_pair<double, 2>(W, c, g, v, tb, nw); break;
     }
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = wave_sum(v[k]);
-    if ((threadIdx.x & 63) == 0) {
+    for (int k = 0; k < 4; k++) v[k] = wave_sum(lane < nw ? v[k] : 0.0);
+    if (lane == 0) {
         double *o = partials + ((size_t)tile * 3 + pair) * 4;
         o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
     }
@@ -144,6 +169,7 @@ extern "C" tgf_status tgf_measure_noalloc(const tgf_geom *geom, const void *link
         return nfail(TGF_E_HIP, std::string("scratch address: ") + hipGetErrorString(e));
     CfgDesc c{};
     for (int m = 0; m < 4; m++) c.d[m] = geom->dims[m];
+    for (int m = 0; m < 3; m++) c.inv[m] = 1.0 / geom->dims[m];
     for (int k = 0; k < 6; k++) c.tw[k] = geom->twist[k];
     c.V = (int)V;
     const int n_tiles = (int)((V + kTile - 1) / kTile);
