@@ -579,7 +579,7 @@ __device__ __forceinline__ void add_raw(const QU16<R> *q, int slot, int k, bool 
 template <class R, int NE>
 struct QuadLinks {
     typedef QuadShape<R, NE> Sh;
-    Links<R, NE> gl;
+    TwoRowLinks<R, NE> gl;
     QuadLds<R, NE> *s;
     int k;                        // this lane's slot in the tile
     bool dn0, dn1, up0, up1;      // every lane finds n - 0, n - 1, n + 0, n + 1 in the tile
@@ -731,9 +731,9 @@ void stage_quad_kernel(StageArgs a) {
     const int mu = __builtin_amdgcn_readfirstlane(((threadIdx.x >> 6) + b) & 3);
 
     const int in = (c.cur + 3 * a.step + a.stage) & 1;
-    QuadLinks<R, NE> W{Links<R, NE>{as_global<R>((const void *)(in ? c.W[1] : c.W[0])), c.stride},
-                       &s, i - tb, false, false, false, false};
-    const OwnLink<R> O{W.gl(mu, i)};
+    const Links<R, NE> G{as_global<R>((const void *)(in ? c.W[1] : c.W[0])), c.stride};
+    QuadLinks<R, NE> W{{G}, &s, i - tb, false, false, false, false};
+    const OwnLink<R> O{G(mu, i)};
     W.put(mu, O.U);
     const Geo g = make_geo_inv(c, i);
     W.dn0 = __all((unsigned)(i + g.dn(0) - tb) < (unsigned)nw);
@@ -992,7 +992,7 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
         const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
-        const Links<R, NE> W{as_global<R>((const void *)(sel ? c.W[1] : c.W[0])), c.stride};
+        const TwoRowLinks<R, NE> W{{as_global<R>((const void *)(sel ? c.W[1] : c.W[0])), c.stride}};
         const Geo g = make_geo_inv(c, i);
         const int nw = min(kTile, c.V - tb);
         switch (pair) {
@@ -1027,7 +1027,7 @@ __global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict_
     __shared__ double part[2][2][kTile];
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
-        const Links<R, NE> W{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride};
+        const TwoRowLinks<R, NE> W{{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride}};
         const Geo g = make_geo_inv(c, i);
         const int nw = min(kTile, c.V - tb);
         switch (pair) {

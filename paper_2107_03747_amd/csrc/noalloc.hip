@@ -9,7 +9,9 @@
 // The kernels are the ones of the context path (measure_dev.h) with a
 // canonical-layout link accessor; the partials have the same (tile, pair)
 // layout and are summed in the same order, so the result equals that of
-// tgf_measure on a TGF_F64_FULL context holding the same links.
+// tgf_measure on a TGF_F64_FULL context holding the same links to rounding
+// (the context, whose links were checked, reads rows 0 and 1 of a link and
+// forms row 2; these links are not checked and are read whole).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -38,7 +40,9 @@ static __device__ __align__(256) double scratch[kScratchDoubles];
 // is entry (64 k + lane) mod 9 of link (64 k + lane) / 9, nine lanes per link,
 // and the entries change lanes through 9 KB of LDS that belong to the wave
 // (its LDS accesses are carried out in order; the fences keep the compiler to
-// it).  Every lane of the wave takes part in every access.
+// it).  Every lane of the wave takes part in every access.  16x16x48x48:
+// 717 us lane by lane at one wave per SIMD, 690 at two (256 registers, eight
+// spilled), 564 this way at two, 985 at three.
 struct CanonLinks {
     const v2<double> *p;
     v2<double> *buf;      // [64][9]
@@ -73,7 +77,7 @@ struct CanonLinks {
 // One work-group per tile of 64 sites, one wave per dual plane pair; the
 // wave's FP64 sums go to partials[tile][pair][4] (as measure_kernel).  Lanes
 // past the last site repeat it and count nothing.
-__global__ __launch_bounds__(192) void measure_canon_kernel(CfgDesc c, const double2 *links,
+__global__ __launch_bounds__(192, 2) void measure_canon_kernel(CfgDesc c, const double2 *links,
                                                             double *partials) {
     __shared__ v2<double> buf[3][64 * 9];
     const int tile = blockIdx.x;
