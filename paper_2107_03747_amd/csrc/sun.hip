@@ -641,7 +641,9 @@ __device__ __forceinline__ void measure_site_n(gptr<const v2<double>> W, const C
 // to at most three work-groups, one wave per group, each summing into one of
 // the tile's three partial slots (the layout of the SU(3) measurement, so the
 // same reduction finishes it); slots that no work-group owns are zero.  One
-// group per wave, for the reason given at SiteGroups.
+// group per wave, for the reason given at SiteGroups.  Each XCD takes a run of
+// tiles, whose neighbours its own L2 then holds (96 boxes 4x4x12x12 of SU(3)
+// 258 -> 216 us per measurement, against tiles dealt round).
 template <int G>
 struct MeasShape {
     static constexpr int P = (kTile + G - 1) / G;         // groups per tile
@@ -650,10 +652,9 @@ struct MeasShape {
 };
 
 // sums v over the work-group's W waves into the slot of this work-group
-template <int G>
+template <int NS, int W>
 __device__ __forceinline__ void store_meas_partials(double v[4], double *__restrict__ partials,
                                                     int tile, int slot) {
-    constexpr int NS = MeasShape<G>::NS, W = MeasShape<G>::W;
     __shared__ double red[W][4];
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = wave_sum_d(v[k]);
@@ -681,8 +682,9 @@ __global__ __launch_bounds__(256) void sun_measure_kernel(const CfgDesc *__restr
                                                           double *__restrict__ partials,
                                                           int buf_sel) {
     constexpr int L = N / R, G = 64 / L, NS = MeasShape<G>::NS, W = MeasShape<G>::W;
-    const int tile = blockIdx.x / NS, slot = blockIdx.x - tile * NS;
-    if (tile >= n_tiles) return;
+    const int b = remap_block(blockIdx.x, NS * n_tiles, 1);   // a run of tiles per XCD
+    if (b >= NS * n_tiles) return;
+    const int tile = b / NS, slot = b - tile * NS;
     const int ci = find_cfg(tile_start, n_cfg, tile);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];     // in global memory: the twist entries are read with run-time indices
@@ -695,7 +697,7 @@ __global__ __launch_bounds__(256) void sun_measure_kernel(const CfgDesc *__restr
     const int site = (tile - tile_start[ci]) * kTile + s0;
     double v[4] = {0, 0, 0, 0};
     if (g < G && s0 < kTile && site < c.V) measure_site_n<N, R>(Wl, c, make_geo(c, site), gr, v);
-    store_meas_partials<G>(v, partials, tile, slot);
+    store_meas_partials<NS, W>(v, partials, tile, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1139,56 +1141,76 @@ __global__ __launch_bounds__(256) void sun_stage_lds_kernel(SunStageArgs a) {
     sun_link_update_lds<N>(a, c, site, mu, q);
 }
 
-// measurement: own row of G_{mu nu}(n) (as clover_blk)
+// measurement: own row of G_{mu nu}(n).  G depends on the leaf sum C only through
+// C - C^+, so a leaf may stand as minus its adjoint: leaves 1 and 2 then share
+// the factor U_mu(n) on the left, leaves 3 and 4 U_mu(n-mu) on the right, ten
+// products where the four leaves take twelve.  The loads of a product stay
+// behind the one before (the scheduler would hold three matrices at N >= 6).
 template <int N>
 __device__ __forceinline__ Row<N> clover_row(gptr<const v2<double>> W, const CfgDesc &c,
                                              const Geo &g, const LaneRow<N> &q, int mu, int nu,
                                              double &rp) {
     const int st = c.stride, r = q.r;
     const int i = g.i, ipm = g.i + g.up(mu), ipn = g.i + g.up(nu);
-    const int imm = g.i + g.dn(mu), imn = g.i + g.dn(nu);
-    Row<N> C = row_zero<N>();
-    // leaf 1: U_mu(n) U_nu(n+mu) U_mu(n+nu)^+ U_nu(n)^+
-    put(q, 1, load_row<N>(W, st, nu, r, ipm));
-    Row<N> t = lmm_nn<N>(load_row<N>(W, st, mu, r, i), q, 1);
+    const int imm = g.i + g.dn(mu), imn = g.i + g.dn(nu), imm_mn = imm + g.dn(nu);
+    // leaf 1: U_mu(n) A, A = U_nu(n+mu) U_mu(n+nu)^+ U_nu(n)^+
     put(q, 1, load_row<N>(W, st, mu, r, ipn));
-    t = lmm_nd<N>(t, q, 1);
+    Row<N> t = lmm_nd<N>(load_row<N>(W, st, nu, r, ipm), q, 1);
     put(q, 1, load_row<N>(W, st, nu, r, i));
     t = lmm_nd<N>(t, q, 1);
     const cx<double> z = leaf_phase<N>(c, mu, nu, g.n(mu), g.n(nu));
-    row_axpy(C, z, t);
-    pin_row(C);
-    rp += cmul(z, own_entry<N>(t, r)).x;
-    // leaf 2: U_nu(n-nu)^+ U_mu(n-nu) U_nu(n+mu-nu) U_mu(n)^+
-    put(q, 0, load_row<N>(W, st, nu, r, imn));
-    put(q, 1, load_row<N>(W, st, mu, r, imn));
-    t = lmm_dn<N>(q, 0, 1);
-    put(q, 1, load_row<N>(W, st, nu, r, imn + g.up(mu)));
-    t = lmm_nn<N>(t, q, 1);
+    Row<N> S = row_zero<N>();
+    row_axpy(S, z, t);
+    pin_row(S);
+    __builtin_amdgcn_sched_barrier(0);
+    // its trace, Re Tr A U_mu(n)
     put(q, 1, load_row<N>(W, st, mu, r, i));
-    t = lmm_nd<N>(t, q, 1);
-    row_axpy(C, leaf_phase<N>(c, mu, nu, g.n(mu), g.back(nu)), t);
+#pragma unroll
+    for (int j = 0; j < N; j++) {
+        const cx<double> u = got(q, 1, j, r);
+        rp = fma(S.e[j].x, u.x, fma(-S.e[j].y, u.y, rp));
+    }
+    asm volatile("" : "+v"(rp)::"memory");
+    __builtin_amdgcn_sched_barrier(0);
+    // leaf 2: U_nu(n-nu)^+ (U_mu(n-nu) U_nu(n+mu-nu)) U_mu(n)^+, as minus its adjoint
+    put(q, 1, load_row<N>(W, st, nu, r, imn + g.up(mu)));
+    t = lmm_nn<N>(load_row<N>(W, st, mu, r, imn), q, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    put(q, 0, t);
+    put(q, 1, load_row<N>(W, st, nu, r, imn));
+    t = lmm_dn<N>(q, 0, 1);
+    const cx<double> z2 = leaf_phase<N>(c, mu, nu, g.n(mu), g.back(nu));
+    row_axpy(S, cx<double>{-z2.x, z2.y}, t);
+    pin_row(S);
+    __builtin_amdgcn_sched_barrier(0);
+    put(q, 1, S);
+    Row<N> C = lmm_nn<N>(load_row<N>(W, st, mu, r, i), q, 1);
     pin_row(C);
+    __builtin_amdgcn_sched_barrier(0);
     // leaf 3: U_nu(n) U_mu(n+nu-mu)^+ U_nu(n-mu)^+ U_mu(n-mu)
     put(q, 1, load_row<N>(W, st, mu, r, ipn + g.dn(mu)));
     t = lmm_nd<N>(load_row<N>(W, st, nu, r, i), q, 1);
+    __builtin_amdgcn_sched_barrier(0);
     put(q, 1, load_row<N>(W, st, nu, r, imm));
     t = lmm_nd<N>(t, q, 1);
-    put(q, 1, load_row<N>(W, st, mu, r, imm));
-    t = lmm_nn<N>(t, q, 1);
-    row_axpy(C, leaf_phase<N>(c, mu, nu, g.back(mu), g.n(nu)), t);
-    pin_row(C);
-    // leaf 4: (U_nu(n-mu-nu) U_mu(n-mu))^+ U_mu(n-mu-nu) U_nu(n-nu)
-    const int imm_mn = imm + g.dn(nu);
-    put(q, 1, load_row<N>(W, st, mu, r, imm));
-    t = lmm_nn<N>(load_row<N>(W, st, nu, r, imm_mn), q, 1);
-    put(q, 0, t);
-    put(q, 1, load_row<N>(W, st, mu, r, imm_mn));
-    t = lmm_dn<N>(q, 0, 1);
+    S = row_zero<N>();
+    row_axpy(S, leaf_phase<N>(c, mu, nu, g.back(mu), g.n(nu)), t);
+    pin_row(S);
+    __builtin_amdgcn_sched_barrier(0);
+    // leaf 4: U_mu(n-mu)^+ U_nu(n-mu-nu)^+ (U_mu(n-mu-nu) U_nu(n-nu)), as minus its adjoint
     put(q, 1, load_row<N>(W, st, nu, r, imn));
-    t = lmm_nn<N>(t, q, 1);
-    row_axpy(C, leaf_phase<N>(c, mu, nu, g.back(mu), g.back(nu)), t);
-    pin_row(C);
+    t = lmm_nn<N>(load_row<N>(W, st, mu, r, imm_mn), q, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    put(q, 0, t);
+    put(q, 1, load_row<N>(W, st, nu, r, imm_mn));
+    t = lmm_dn<N>(q, 0, 1);
+    const cx<double> z4 = leaf_phase<N>(c, mu, nu, g.back(mu), g.back(nu));
+    row_axpy(S, cx<double>{-z4.x, z4.y}, t);
+    pin_row(S);
+    __builtin_amdgcn_sched_barrier(0);
+    put(q, 1, load_row<N>(W, st, mu, r, imm));
+    t = lmm_nn<N>(S, q, 1);
+    row_axpy(C, cx<double>{1.0, 0.0}, t);
     // G = -(i/8)(C - C^+): own row of C - C^+ is C_r - conj(column r of C)
     put(q, 0, C);
     Row<N> Gr;
@@ -1210,13 +1232,14 @@ __device__ __forceinline__ double row_dot(const Row<N> &a, const Row<N> &b) {
 }
 
 // this lane's share of e(n), q(n), the plaquette sum and the action density
-// (as measure_site_n)
+// (as measure_site_n), from the plane pairs pr0 .. pr1 - 1
 template <int N>
 __device__ __forceinline__ void measure_site_lds(gptr<const v2<double>> W, const CfgDesc &c,
-                                                 const Geo &g, const LaneRow<N> &q, double v[4]) {
+                                                 const Geo &g, const LaneRow<N> &q, int pr0,
+                                                 int pr1, double v[4]) {
     double e = 0.0, qq = 0.0, p = 0.0;
 #pragma unroll 1
-    for (int pr = 0; pr < 3; pr++) {
+    for (int pr = pr0; pr < pr1; pr++) {
         const int a1 = pr + 1;
         const int b0 = pr == 2 ? 1 : (pr == 1 ? 1 : 2);
         const int b1 = pr == 0 ? 3 : (pr == 1 ? 3 : 2);
@@ -1229,21 +1252,38 @@ __device__ __forceinline__ void measure_site_lds(gptr<const v2<double>> W, const
     v[0] += e;
     v[1] += qq * 0.025330295910584444;   // 1 / (4 pi^2)
     v[2] += p;
-    v[3] += 6.0 - p;
+    v[3] += 2.0 * (pr1 - pr0) - p;
 }
 
+// How the work-groups of a tile share it: all the tile's site groups and one
+// plane pair each (a third of the serial chain per wave), as long as two such
+// work-groups fit the 160 KB LDS of a CU (N <= 5); above that the groups are
+// dealt out as MeasShape does and a wave takes the three pairs in turn.
+// Measured with the ten-product leaves and a run of tiles per XCD: one
+// 3x3x15x15 box of SU(5) 69 -> 30 us, 24 of 4x4x20x20 941 -> 884; one
+// 3x3x18x18 box of SU(6) 91 -> 81 us, 8 of 4x4x24x24 879 -> 742.
 template <int N>
-__global__ __launch_bounds__(256) void sun_measure_lds_kernel(const CfgDesc *__restrict__ cfgs,
+struct LdsMeas {
+    static constexpr int P = MeasShape<LdsShape<N>::G>::P;
+    static constexpr bool kPair = 2 * LdsShape<N>::SLOT * 16 * P <= 80000;
+    static constexpr int NS = kPair ? 3 : MeasShape<LdsShape<N>::G>::NS;
+    static constexpr int W = kPair ? P : MeasShape<LdsShape<N>::G>::W;
+};
+
+template <int N>
+__global__ __launch_bounds__(LdsMeas<N>::W < 4 ? 256 : 64 * LdsMeas<N>::W) void sun_measure_lds_kernel(const CfgDesc *__restrict__ cfgs,
                                                               const int *__restrict__ tile_start,
                                                               int n_cfg, int n_tiles,
                                                               const MeasSlot *__restrict__ slots,
                                                               double *__restrict__ partials,
                                                               int buf_sel) {
     constexpr int G = LdsShape<N>::G, SLOT = LdsShape<N>::SLOT, LS = LdsShape<N>::LS;
-    constexpr int NS = MeasShape<G>::NS, W = MeasShape<G>::W;
+    constexpr int NS = LdsMeas<N>::NS, W = LdsMeas<N>::W;
+    constexpr bool kPair = LdsMeas<N>::kPair;
     __shared__ v2<double> lds[W][2][SLOT];
-    const int tile = blockIdx.x / NS, slot = blockIdx.x - tile * NS;
-    if (tile >= n_tiles) return;
+    const int b = remap_block(blockIdx.x, NS * n_tiles, 1);   // a run of tiles per XCD
+    if (b >= NS * n_tiles) return;
+    const int tile = b / NS, slot = b - tile * NS;
     const int ci = find_cfg(tile_start, n_cfg, tile);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];     // in global memory: the twist entries are read with run-time indices
@@ -1253,11 +1293,12 @@ __global__ __launch_bounds__(256) void sun_measure_lds_kernel(const CfgDesc *__r
     const int g = lane / N;
     const int gg = g < G ? g : 0;            // lanes past the last link: no slot
     const LaneRow<N> q{{&lds[w][0][gg * LS], &lds[w][1][gg * LS]}, lane - g * N, g * N};
-    const int s0 = (slot * W + w) * G + g;
+    const int s0 = ((kPair ? 0 : slot * W) + w) * G + g;
     const int site = (tile - tile_start[ci]) * kTile + s0;
     double v[4] = {0, 0, 0, 0};
-    if (g < G && s0 < kTile && site < c.V) measure_site_lds<N>(Wl, c, make_geo(c, site), q, v);
-    store_meas_partials<G>(v, partials, tile, slot);
+    if (g < G && s0 < kTile && site < c.V)
+        measure_site_lds<N>(Wl, c, make_geo(c, site), q, kPair ? slot : 0, kPair ? slot + 1 : 3, v);
+    store_meas_partials<NS, W>(v, partials, tile, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1323,14 +1364,15 @@ static hipError_t stage_nr(hipStream_t s, const SunStageArgs &a) {
 template <int N, int R>
 static hipError_t measure_nr(hipStream_t s, const CfgDesc *cfgs, const int *tile_start, int n_cfg,
                              int n_tiles, const MeasSlot *slots, double *partials, int buf_sel) {
-    typedef MeasShape<links_per_wave<N, R>()> Sh;
-    const dim3 grid(n_tiles * Sh::NS), block(64 * Sh::W);
-    if constexpr (R == kLds)
-        hipLaunchKernelGGL((sun_measure_lds_kernel<N>), grid, block, 0, s, cfgs, tile_start, n_cfg,
-                           n_tiles, slots, partials, buf_sel);
-    else
-        hipLaunchKernelGGL((sun_measure_kernel<N, R>), grid, block, 0, s, cfgs, tile_start, n_cfg,
-                           n_tiles, slots, partials, buf_sel);
+    if constexpr (R == kLds) {
+        typedef LdsMeas<N> Sh;
+        hipLaunchKernelGGL((sun_measure_lds_kernel<N>), dim3((n_tiles * Sh::NS + 7) / 8 * 8),
+                           dim3(64 * Sh::W), 0, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
+    } else {
+        typedef MeasShape<links_per_wave<N, R>()> Sh;
+        hipLaunchKernelGGL((sun_measure_kernel<N, R>), dim3((n_tiles * Sh::NS + 7) / 8 * 8),
+                           dim3(64 * Sh::W), 0, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
+    }
     return hipGetLastError();
 }
 

@@ -56,3 +56,27 @@ def test_exponential_branches(N, eps):
 @pytest.mark.parametrize("N", [2, 3, 4, 5, 6, 7, 8])
 def test_ragged_groups_all_planes_twisted(N, dims):
     one_step_all_variants(N, dims, (1, N - 1, 1, N // 2, 1, N - 1), 0.02)
+
+
+@pytest.mark.parametrize("dims", [(3, 3, 3, 3), (2, 3, 3, 5)])
+@pytest.mark.parametrize("N", [2, 3, 4, 5, 6, 7, 8])
+def test_measurement_of_ragged_tiles_all_planes_twisted(N, dims):
+    """Rows of every variant's measurement on boxes of two part-filled tiles
+    (81 and 90 sites; work-groups own a plane pair, or a part of the sites).
+    An entry of a leaf is off by at most 2 (3 N) ulps, so is one of G; the
+    density sums 6 N^2 products of two such entries of size below one."""
+    tw = (1, N - 1, 1, N // 2, 1, N - 1)
+    U = gen.near_identity_n(dims, N, 0.5, seed=31 + N).numpy().copy()
+    ref = oracle.sun_measure(U, dims, twist=tw)
+    V = int(np.prod(dims))
+    ulp = 6 * N * 2.0 ** -52
+    tol = {1: 12 * N * N * ulp, 3: ulp, 4: V * 6 * N * N * ulp, 5: 6 * N * V * ulp}
+    for v in range(tgf.tgf_sun_variant_count(N)):
+        f = tgf.Flow([(dims, tw)], "f64", nc=N)
+        f.set_variant(v)
+        f.load(0, torch.from_numpy(U).cuda())
+        row = np.asarray(f.measure())[0]
+        for col, key in ((1, "E"), (3, "plaq"), (4, "Q"), (5, "action")):
+            d = abs(float(row[col]) - float(ref[key]))
+            print(f"  SU({N}) {dims} variant {v} {key}: off {d:.3g} (tol {tol[col]:.3g})", flush=True)
+            assert d <= tol[col]
