@@ -1014,7 +1014,12 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
 // q(n) = (1/16 pi^2) Tr G G~, written to FP64 arrays in site order (either may
 // be null).  As the measurement: a work-group is one tile, one wave per dual
 // plane pair, leaves taken from the wave where it holds the neighbour; the
-// three pairs meet in LDS.  to_x: q(n) goes to the configuration's accumulator
+// three pairs meet in LDS.  Each XCD takes a run of tiles (large boxes' in
+// columns), so that a tile finds its neighbours in its L2: FP64 16x16x48x48
+// 258 -> 244 us, 12x12x36x36 111 -> 94, FP32 16x16x48x48 140 -> 122.  (The
+// measurement above deals its tiles round: runs slowed the 96-box ensemble
+// by 14%, 810 -> 922 us, and gained nothing on one 16x16x48x48 box.)
+// to_x: q(n) goes to the configuration's accumulator
 // buffer, which a flow writes before it reads it, for the slice sums below.
 template <class R, int NE>
 __global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict__ cfgs, int ci,
@@ -1023,7 +1028,9 @@ __global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict_
     const CfgDesc c = cfgs[ci];
     if (to_x) q_out = (double *)c.X;
     const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int tb = blockIdx.x * kTile, i = tb + lane;
+    const int nt = (c.V + kTile - 1) / kTile, b = remap_block(blockIdx.x, nt, 1);
+    if (b >= nt) return;
+    const int tb = tile_order(b, c) * kTile, i = tb + lane;
     __shared__ double part[2][2][kTile];
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
@@ -1494,7 +1501,7 @@ hipError_t launch_check_final(hipStream_t s, const double *partials, int ntiles,
 
 static hipError_t densities(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs, int ci, int V,
                             double *e_out, double *q_out, int to_x) {
-    const dim3 grid((V + kTile - 1) / kTile);
+    const dim3 grid(((V + kTile - 1) / kTile + 7) / 8 * 8);
     if (p == P_F64)
         hipLaunchKernelGGL((density_kernel<double, 9>), grid, dim3(192), 0, s, cfgs, ci, e_out,
                            q_out, to_x);
