@@ -338,15 +338,15 @@ def time_mc(tgf, torch, cfgs, inputs, reps, cpu=True):
 # General SU(N) (FP64, row-per-lane kernels), per site per RK3 step.
 # Bytes: links read + written every stage, 3 x 2 x 4 x N^2 x 16, and the full
 # N x N accumulator X written, read + written, read: 4 x 4 x N^2 x 16.
-# Flops: per link and stage 25 N x N products (6 staples of 2, U S, 11 Horner
-# steps of the exponential, exp(X) U) of 8 N^3 flop, plus the staple sums
+# Flops: per link and stage 19 N x N products (6 staples of 2, U S, about 5 of
+# the exponential's polynomial, exp(X) U) of 8 N^3 flop, plus the staple sums
 # (6 N^2 complex multiply-adds), P_ah and the RK update (~2 N^2 of them).
 def sun_bytes_per_site_step(N):
     return 3 * 2 * 4 * N * N * 16 + 4 * 4 * N * N * 16
 
 
 def sun_flops_per_site_step(N):
-    return 4 * 3 * (25 * 8 * N ** 3 + 8 * 8 * N * N)
+    return 4 * 3 * (19 * 8 * N ** 3 + 8 * 8 * N * N)
 
 
 def sun_mode(tgf, torch, args):

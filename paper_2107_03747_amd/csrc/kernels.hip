@@ -717,7 +717,8 @@ template <class R, int NE>
 __global__ __launch_bounds__(256, sizeof(R) == 8 ? 2 : (NE == 9 ? 4 : 5))
 void stage_quad_kernel(StageArgs a) {
     __shared__ QuadLds<R, NE> s;
-    const int b = remap_block(blockIdx.x, a.n_tiles, a.xcd);
+    const int b = a.n_act > 1 ? deal_block(blockIdx.x, a.n_tiles, a.xcd)
+                              : remap_block(blockIdx.x, a.n_tiles, a.xcd);
     if (b >= a.n_tiles) return;                            // whole work-group
     const int ci = find_cfg(a.tile_start, a.n_act, b);
     const CfgDesc c = a.cfgs[ci];
@@ -974,7 +975,12 @@ __global__ __launch_bounds__(256) void stage_link_kernel(StageArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// measurement: clover G (eq. gmunu), e(n), q(n), plaquette, action (measure_dev.h)
+// measurement: clover G (eq. gmunu), e(n), q(n), plaquette, action (measure_dev.h).
+// Each XCD takes a run of every configuration's tiles: 64, 16 and 16 boxes of
+// L = 8, 6, 10 in 12-real storage 750 -> 699 us, 24, 8 and 2 of L = 8, 6, 12 in
+// FP64 535 -> 503, against tiles dealt round.  (A run of the whole launch per
+// XCD: 922 us; the extents differ in cost, and events that measure some of the
+// configurations leave XCDs without work.)
 
 template <class R, int NE>
 __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict__ cfgs,
@@ -987,7 +993,8 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
     const int ci = find_cfg(tile_start, n_cfg, tile);
     if (slots[ci].row < 0) return;
     const CfgDesc c = cfgs[ci];
-    const int tb = (tile - tile_start[ci]) * kTile;            // site of lane 0
+    const int at = tile_order(run_order(tile - tile_start[ci], (c.V + kTile - 1) / kTile), c);
+    const int tb = at * kTile;                                 // site of lane 0
     const int i = tb + (threadIdx.x & 63);
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
@@ -1004,7 +1011,7 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
 #pragma unroll
     for (int k = 0; k < 4; k++) v[k] = wave_sum(v[k]);
     if ((threadIdx.x & 63) == 0) {
-        double *o = partials + ((size_t)tile * 3 + pair) * 4;
+        double *o = partials + ((size_t)(tile_start[ci] + at) * 3 + pair) * 4;
         o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
     }
 }
@@ -1028,9 +1035,7 @@ __global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict_
     const CfgDesc c = cfgs[ci];
     if (to_x) q_out = (double *)c.X;
     const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int nt = (c.V + kTile - 1) / kTile, b = remap_block(blockIdx.x, nt, 1);
-    if (b >= nt) return;
-    const int tb = tile_order(b, c) * kTile, i = tb + lane;
+    const int tb = tile_order(run_order(blockIdx.x, gridDim.x), c) * kTile, i = tb + lane;
     __shared__ double part[2][2][kTile];
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
@@ -1501,7 +1506,7 @@ hipError_t launch_check_final(hipStream_t s, const double *partials, int ntiles,
 
 static hipError_t densities(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs, int ci, int V,
                             double *e_out, double *q_out, int to_x) {
-    const dim3 grid(((V + kTile - 1) / kTile + 7) / 8 * 8);
+    const dim3 grid((V + kTile - 1) / kTile);
     if (p == P_F64)
         hipLaunchKernelGGL((density_kernel<double, 9>), grid, dim3(192), 0, s, cfgs, ci, e_out,
                            q_out, to_x);

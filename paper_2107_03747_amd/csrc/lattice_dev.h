@@ -191,6 +191,35 @@ __host__ __device__ __forceinline__ int remap_block(int b, int nb, int xcd) {
     return (b & 7) * per + (b >> 3);
 }
 
+// The same for launches over several configurations: chunks of kDeal blocks are
+// dealt to the XCDs in turn and the rest (all of a small launch) in runs, so
+// that each XCD has a share of every extent.  With a run of the whole launch
+// each, the XCDs that held the extents whose tiles cost most (L = 10: 0.21 ns
+// per site in 12-real storage, L = 8: 0.17) ended last.  Stage launch of 64, 16
+// and 16 boxes of L = 8, 6, 10, runs -> chunks of 256 / 512 / 1024 / 2048
+// tiles: 12-real 803 -> 729 / 726 / 739 / 739 us, FP32 full 1060 -> 893 / 911 /
+// 929 / 931; of 24, 8 and 2 boxes of L = 8, 6, 12 in FP64: 664 -> 612 / 610 /
+// 628 / 664.  96 boxes of one extent pay 1% (579 -> 585) for
+// the ends of the chunks.
+constexpr int kDeal = 512;
+__host__ __device__ __forceinline__ int deal_block(int b, int nb, int xcd) {
+    if (!xcd) return b;
+    const int full = nb / (8 * kDeal) * (8 * kDeal);
+    if (b >= full) return full + remap_block(b - full, nb - full, 1);
+    const int i = b >> 3, q = i / kDeal;
+    return (q * 8 + (b & 7)) * kDeal + (i - q * kDeal);
+}
+
+// Place of the j-th of one configuration's n work-groups in its site order when
+// each XCD (j mod 8, up to a rotation) takes a run of them: one-to-one on
+// 0 .. n - 1.  Unlike a run of the whole launch per XCD, this spreads every
+// configuration over all XCDs, whichever of them a launch works on and
+// whatever their tiles cost.
+__host__ __device__ __forceinline__ int run_order(int j, int n) {
+    const int k = j & 7, q = n >> 3, r = n & 7;
+    return k * q + (k < r ? k : r) + (j >> 3);
+}
+
 // wave-uniform: which config (exec order) holds tile t (also the block
 // table of the LDS-staged variants)
 __host__ __device__ __forceinline__ int find_cfg(const int *__restrict__ tile_start, int n, int t) {

@@ -81,8 +81,7 @@ struct CanonLinks {
 __global__ __launch_bounds__(192, 2) void measure_canon_kernel(CfgDesc c, const double2 *links,
                                                             double *partials) {
     __shared__ v2<double> buf[3][64 * 9];
-    const int nt = (c.V + kTile - 1) / kTile, tile = remap_block(blockIdx.x, nt, 1);
-    if (tile >= nt) return;
+    const int tile = run_order(blockIdx.x, gridDim.x);
     const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int tb = tile * kTile;                               // site of lane 0
     const int nw = min(kTile, c.V - tb);
@@ -180,7 +179,7 @@ extern "C" tgf_status tgf_measure_noalloc(const tgf_geom *geom, const void *link
     c.V = (int)V;
     const int n_tiles = (int)((V + kTile - 1) / kTile);
     hipStream_t s = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(measure_canon_kernel, dim3((n_tiles + 7) / 8 * 8), dim3(192), 0, s, c,
+    hipLaunchKernelGGL(measure_canon_kernel, dim3(n_tiles), dim3(192), 0, s, c,
                        (const double2 *)links_dev, part);
     e = hipGetLastError();
     if (e == hipSuccess) {

@@ -642,8 +642,10 @@ __device__ __forceinline__ void measure_site_n(gptr<const v2<double>> W, const C
 // the tile's three partial slots (the layout of the SU(3) measurement, so the
 // same reduction finishes it); slots that no work-group owns are zero.  One
 // group per wave, for the reason given at SiteGroups.  Each XCD takes a run of
-// tiles, whose neighbours its own L2 then holds (96 boxes 4x4x12x12 of SU(3)
-// 258 -> 216 us per measurement, against tiles dealt round).
+// every configuration's tiles, whose neighbours its own L2 then holds (96 boxes
+// 4x4x12x12 of SU(3) 258 -> 216 us per measurement with runs of the launch,
+// against tiles dealt round; runs of a configuration cost 2% more than that
+// and keep all XCDs busy when an event measures some of the configurations).
 template <int G>
 struct MeasShape {
     static constexpr int P = (kTile + G - 1) / G;         // groups per tile
@@ -682,12 +684,11 @@ __global__ __launch_bounds__(256) void sun_measure_kernel(const CfgDesc *__restr
                                                           double *__restrict__ partials,
                                                           int buf_sel) {
     constexpr int L = N / R, G = 64 / L, NS = MeasShape<G>::NS, W = MeasShape<G>::W;
-    const int b = remap_block(blockIdx.x, NS * n_tiles, 1);   // a run of tiles per XCD
-    if (b >= NS * n_tiles) return;
-    const int tile = b / NS, slot = b - tile * NS;
-    const int ci = find_cfg(tile_start, n_cfg, tile);
+    const int ci = find_cfg(tile_start, n_cfg, blockIdx.x / NS);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];     // in global memory: the twist entries are read with run-time indices
+    const int b = run_order(blockIdx.x - NS * tile_start[ci], NS * ((c.V + kTile - 1) / kTile));
+    const int tile = tile_start[ci] + b / NS, slot = b % NS;
     const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
     gptr<const v2<double>> Wl = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1281,12 +1282,11 @@ __global__ __launch_bounds__(LdsMeas<N>::W < 4 ? 256 : 64 * LdsMeas<N>::W) void 
     constexpr int NS = LdsMeas<N>::NS, W = LdsMeas<N>::W;
     constexpr bool kPair = LdsMeas<N>::kPair;
     __shared__ v2<double> lds[W][2][SLOT];
-    const int b = remap_block(blockIdx.x, NS * n_tiles, 1);   // a run of tiles per XCD
-    if (b >= NS * n_tiles) return;
-    const int tile = b / NS, slot = b - tile * NS;
-    const int ci = find_cfg(tile_start, n_cfg, tile);
+    const int ci = find_cfg(tile_start, n_cfg, blockIdx.x / NS);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];     // in global memory: the twist entries are read with run-time indices
+    const int b = run_order(blockIdx.x - NS * tile_start[ci], NS * ((c.V + kTile - 1) / kTile));
+    const int tile = tile_start[ci] + b / NS, slot = b % NS;
     const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
     gptr<const v2<double>> Wl = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1366,12 +1366,12 @@ static hipError_t measure_nr(hipStream_t s, const CfgDesc *cfgs, const int *tile
                              int n_tiles, const MeasSlot *slots, double *partials, int buf_sel) {
     if constexpr (R == kLds) {
         typedef LdsMeas<N> Sh;
-        hipLaunchKernelGGL((sun_measure_lds_kernel<N>), dim3((n_tiles * Sh::NS + 7) / 8 * 8),
-                           dim3(64 * Sh::W), 0, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
+        hipLaunchKernelGGL((sun_measure_lds_kernel<N>), dim3(n_tiles * Sh::NS), dim3(64 * Sh::W), 0,
+                           s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
     } else {
         typedef MeasShape<links_per_wave<N, R>()> Sh;
-        hipLaunchKernelGGL((sun_measure_kernel<N, R>), dim3((n_tiles * Sh::NS + 7) / 8 * 8),
-                           dim3(64 * Sh::W), 0, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
+        hipLaunchKernelGGL((sun_measure_kernel<N, R>), dim3(n_tiles * Sh::NS), dim3(64 * Sh::W), 0,
+                           s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
     }
     return hipGetLastError();
 }

@@ -489,8 +489,8 @@ __device__ __forceinline__ Zm clover_mx(gptr<const v2<double>> W, const CfgDesc 
 }
 
 // A tile's 64 / G groups are dealt to three work-groups (partial slots) of W
-// waves, K groups one after another in a wave.  Each XCD takes a run of tiles
-// (48 boxes 4x4x16x16 of SU(4) 311 -> 286 us, 6 of 4x4x28x28 of SU(7) 698 -> 668).
+// waves, K groups one after another in a wave.  Each XCD takes a run of
+// every configuration's tiles (48 boxes 4x4x16x16 of SU(4) 311 -> 293 us).
 template <int N>
 struct MxMeas {
     static constexpr int P = kTile / Mx<N>::G;
@@ -503,12 +503,11 @@ __global__ __launch_bounds__(64 * MxMeas<N>::W) void sun_measure_mfma_kernel(
     const CfgDesc *__restrict__ cfgs, const int *__restrict__ tile_start, int n_cfg, int n_tiles,
     const MeasSlot *__restrict__ slots, double *__restrict__ partials, int buf_sel) {
     constexpr int G = Mx<N>::G, W = MxMeas<N>::W, K = MxMeas<N>::K;
-    const int b = remap_block(blockIdx.x, 3 * n_tiles, 1);   // a run of tiles per XCD
-    if (b >= 3 * n_tiles) return;
-    const int tile = b / 3, slot = b - tile * 3;
-    const int ci = find_cfg(tile_start, n_cfg, tile);
+    const int ci = find_cfg(tile_start, n_cfg, blockIdx.x / 3);
     if (slots[ci].row < 0) return;
     const CfgDesc &c = cfgs[ci];
+    const int b = run_order(blockIdx.x - 3 * tile_start[ci], 3 * ((c.V + kTile - 1) / kTile));
+    const int tile = tile_start[ci] + b / 3, slot = b % 3;
     const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
     gptr<const v2<double>> L = as_global<double>((const void *)(sel ? c.W[1] : c.W[0]));
     const int t0 = (tile - tile_start[ci]) * kTile;
@@ -573,8 +572,8 @@ hipError_t launch_stage_sun_mfma(int nc, hipStream_t s, const SunStageArgs &a) {
 template <int N>
 static hipError_t measure_n(hipStream_t s, const CfgDesc *cfgs, const int *tile_start, int n_cfg,
                             int n_tiles, const MeasSlot *slots, double *partials, int buf_sel) {
-    hipLaunchKernelGGL((sun_measure_mfma_kernel<N>), dim3((3 * n_tiles + 7) / 8 * 8),
-                       dim3(64 * MxMeas<N>::W), 0, s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
+    hipLaunchKernelGGL((sun_measure_mfma_kernel<N>), dim3(3 * n_tiles), dim3(64 * MxMeas<N>::W), 0,
+                       s, cfgs, tile_start, n_cfg, n_tiles, slots, partials, buf_sel);
     return hipGetLastError();
 }
 hipError_t launch_measure_sun_mfma(int nc, hipStream_t s, const CfgDesc *cfgs,

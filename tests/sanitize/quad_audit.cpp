@@ -90,7 +90,33 @@ static void columns(std::array<int, 4> d, int chunk) {
     }
 }
 
+// Launch orders: every block of a launch (padded to a multiple of eight) once,
+// the padding past the end, whatever the number of blocks.
+static void orders(int n) {
+    std::vector<char> runs(n, 0), deal(n, 0);
+    int live = 0, wrong = 0;
+    for (int j = 0; j < n; j++) {
+        const int t = run_order(j, n);
+        if (t < 0 || t >= n || runs[t]++) wrong++;
+    }
+    for (int b = 0; b < (n + 7) / 8 * 8; b++) {
+        const int t = deal_block(b, n, 1);
+        if (t >= n) continue;
+        live++;
+        if (t < 0 || deal[t]++) wrong++;
+    }
+    checked += 2 * n;
+    if (live != n || wrong) {
+        std::fprintf(stderr, "violation: launch order of %d blocks\n", n);
+        bad++;
+    }
+}
+
 int main() {
+    for (int n = 1; n < 200; n++) orders(n);
+    for (int n : {8 * kDeal - 1, 8 * kDeal, 8 * kDeal + 1, 8 * kDeal + 7, 16 * kDeal + 13, 62400,
+                  147456, 524287})
+        orders(n);
     columns({16, 16, 48, 48}, 16);
     columns({32, 32, 96, 12}, 64);
     columns({20, 20, 60, 5}, 25);

@@ -1,6 +1,7 @@
 """The quad stage kernel's index arithmetic on the host (CPU only): coordinates
 by products with 1/d against integer division, up to the site cap, and the LDS
-slots of every tile (tests/sanitize/quad_audit.cpp), under the host sanitizers."""
+slots of every tile, and the launch orders as one-to-one maps
+(tests/sanitize/quad_audit.cpp), under the host sanitizers."""
 
 import os
 import subprocess
