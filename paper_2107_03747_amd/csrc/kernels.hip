@@ -513,9 +513,9 @@ void stage_site_lds_kernel(StageArgs a) {
 //
 // Why, against one thread per site over 256-site blocks (stage_site_lds_kernel):
 //   - a site's chain of loops is a quarter as long and a small box fills four
-//     times the waves: 4x4x12x12 12-real 22.3 -> 9.0 us per stage, 6x6x18x18
-//     FP64 31.9 -> 14.3 us;
-//   - a wave holds one link's force (90 / 106 / 197 registers against 141 / 211 /
+//     times the waves: 4x4x12x12 12-real 22.3 -> 7.3 us per stage, 6x6x18x18
+//     FP64 31.9 -> 11.9 us;
+//   - a wave holds one link's force (90 / 106 / 182 registers against 141 / 211 /
 //     490), so five, four and two waves share a SIMD instead of three, two and
 //     one: non-packed FP32 instructions of two waves issue together (2.1 cycles
 //     per instruction and SIMD with an even number of waves, 4.2 with one);
@@ -523,8 +523,8 @@ void stage_site_lds_kernel(StageArgs a) {
 //     of 1.98 GB past the L2 per launch on the 96-configuration batch.
 // Stage launch, 3.5e6 sites of 8x8x24x24, 10x10x30x30, 16x16x48x48 in turn:
 // 12-real 613 -> 590, 824 -> 770, 709 -> 700 us (12x12x36x36 1020 -> 800);
-// FP32 full 865 -> 700, 1020 -> 1005, 980 -> 900; FP64 1940 -> 1450, 2360 ->
-// 1990, 2725 -> 1785.  Under this load the clock falls to 1.4-1.6 GHz, so what
+// FP32 full 865 -> 700, 1020 -> 1005, 980 -> 900; FP64 1940 -> 1400, 2360 ->
+// 1912, 2725 -> 1670.  Under this load the clock falls to 1.4-1.6 GHz, so what
 // is left is energy: operations and bytes moved, not waves or latency.  Tried:
 // third rows of 12-real links kept in LDS (-6% instructions, 33 KB) +7%; six
 // waves per SIMD (own link re-read from LDS) +2%; links requested two or three
