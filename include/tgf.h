@@ -352,7 +352,7 @@ const char *tgf_stats_last_error(void);
  * Arguments are checked on the host; then two kernels are enqueued and the
  * call returns without synchronising.  A non-finite sum shows as non-finite
  * entries of *out_dev (there is no status word).  The result equals that of
- * tgf_measure on a TGF_F64_FULL context holding the same links, to rounding. */
+ * tgf_measure on a TGF_F64_FULL context holding the same links. */
 #define TGF_NOALLOC_MAX_SITES 12582912
 tgf_status tgf_measure_noalloc(const tgf_geom *geom, const void *links_dev, double t,
                                tgf_obs *out_dev, void *hip_stream);

@@ -514,8 +514,8 @@ void stage_site_lds_kernel(StageArgs a) {
 // Why, against one thread per site over 256-site blocks (stage_site_lds_kernel):
 //   - a site's chain of loops is a quarter as long and a small box fills four
 //     times the waves: 4x4x12x12 12-real 22.3 -> 7.3 us per stage, 6x6x18x18
-//     FP64 31.9 -> 11.9 us;
-//   - a wave holds one link's force (90 / 106 / 182 registers against 141 / 211 /
+//     FP64 32.8 -> 15.1 us;
+//   - a wave holds one link's force (90 / 106 / 240 registers against 141 / 211 /
 //     490), so five, four and two waves share a SIMD instead of three, two and
 //     one: non-packed FP32 instructions of two waves issue together (2.1 cycles
 //     per instruction and SIMD with an even number of waves, 4.2 with one);
@@ -523,8 +523,8 @@ void stage_site_lds_kernel(StageArgs a) {
 //     of 1.98 GB past the L2 per launch on the 96-configuration batch.
 // Stage launch, 3.5e6 sites of 8x8x24x24, 10x10x30x30, 16x16x48x48 in turn:
 // 12-real 613 -> 590, 824 -> 770, 709 -> 700 us (12x12x36x36 1020 -> 800);
-// FP32 full 865 -> 700, 1020 -> 1005, 980 -> 900; FP64 1940 -> 1400, 2360 ->
-// 1912, 2725 -> 1670.  Under this load the clock falls to 1.4-1.6 GHz, so what
+// FP32 full 865 -> 700, 1020 -> 1005, 980 -> 900; FP64 2110 -> 1504, 2440 ->
+// 2016, 2795 -> 1719.  Under this load the clock falls to 1.4-1.6 GHz, so what
 // is left is energy: operations and bytes moved, not waves or latency.  Tried:
 // third rows of 12-real links kept in LDS (-6% instructions, 33 KB) +7%; six
 // waves per SIMD (own link re-read from LDS) +2%; links requested two or three
@@ -579,7 +579,7 @@ __device__ __forceinline__ void add_raw(const QU16<R> *q, int slot, int k, bool 
 template <class R, int NE>
 struct QuadLinks {
     typedef QuadShape<R, NE> Sh;
-    TwoRowLinks<R, NE> gl;
+    Links<R, NE> gl;
     QuadLds<R, NE> *s;
     int k;                        // this lane's slot in the tile
     bool dn0, dn1, up0, up1;      // every lane finds n - 0, n - 1, n + 0, n + 1 in the tile
@@ -634,17 +634,36 @@ struct QuadLinks {
     }
 };
 
-// Raw form of the upper plaquette of plane (A, B) at n.
+// Raw form of the upper plaquette of plane (A, B) at n.  FP32 forms rows 0 and
+// 1 and takes the third as conj(row0 x row1).  FP64 forms all three rows here
+// and in the lower staples, and reads links whole: a load accepts links that
+// are SU(3) to 1e-10, and a row that is left out and rebuilt would be another
+// one.  Against 80-bit arithmetic 16 steps then err 1.40e-16 rms (1.45e-16 with
+// rebuilt rows, 1.42e-16 in stage_site_lds_kernel), and links with a defect of
+// 2e-11 come out 5e-13 from the plain products per step of 0.02 (1.1e-12 and
+// 7e-13; what is left is the conjugation of quad_pass, none where tiles are not
+// closed).  It costs 3 to 8% of a stage launch: 96 boxes of 8x8x24x24 1400 ->
+// 1504 us, 40 of 10x10x30x30 1850 -> 2016 us.
 template <class R, int NE, int A, int B>
 __device__ __forceinline__ void quad_plane(const QuadLinks<R, NE> &W, const CfgDesc &c,
                                            const Geo &g, R r[8]) {
-    R2<R> P = r2_of(W.own(A));
-    P = r2_mul_nn(P, W.up(B, A, g));
-    P = r2_mul_nd(P, W.up(A, B, g));
-    P = r2_mul_nd(P, W.own(B));
     const int k = c.tw[plane_index(A, B)];
-    if (k && g.n(A) == 0 && g.n(B) == 0) r2_scale(P, cconj(omega_pow<R>(k)));
-    r2_raw(P, r);
+    const bool tw = k && g.n(A) == 0 && g.n(B) == 0;
+    if constexpr (sizeof(R) == 8) {
+        M3<R> P = W.own(A);
+        P = mul_nn(P, W.up(B, A, g));
+        P = mul_nd(P, W.up(A, B, g));
+        P = mul_nd(P, W.own(B));
+        if (tw) m_scale(P, cconj(omega_pow<R>(k)));
+        m_raw(P, r);
+    } else {
+        R2<R> P = r2_of(W.own(A));
+        P = r2_mul_nn(P, W.up(B, A, g));
+        P = r2_mul_nd(P, W.up(A, B, g));
+        P = r2_mul_nd(P, W.own(B));
+        if (tw) r2_scale(P, cconj(omega_pow<R>(k)));
+        r2_raw(P, r);
+    }
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -689,6 +708,28 @@ __device__ __forceinline__ void quad_terms(const QuadLinks<R, NE> &W, const CfgD
         if (W.dn1) quad_pass<R, NE>(W, g, r, 1, MU + 1, false, f);
         put_raw<R>(W.s->raw, MU + 1, W.k, r);
     }
+    if constexpr (sizeof(R) == 8) {
+        // the staples summed as matrices (three rows, see quad_plane), then U_mu S
+        M3<R> S;
+        m_zero(S);
+#pragma unroll
+        for (int nu = 0; nu < 4; nu++) {
+            if (nu == MU || (nu == 0 && W.dn0) || (nu == 1 && W.dn1)) continue;
+            __builtin_amdgcn_sched_barrier(0);
+            const int imn = g.i + g.dn(nu);
+            M3<R> T = mul_nn(W.gl(MU, imn), W.gl(nu, imn + g.up(MU)));
+            const int k = twist_exp(c, MU, nu);
+            if (k && g.n(MU) == 0 && g.back(nu) == 0) m_scale(T, cconj(omega_pow<R>(k)));
+            __builtin_amdgcn_sched_barrier(0);
+            m_acc_mul_dn(S, T, W.gl(nu, imn));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        m_raw(mul_nn(W.own(MU), S), r);
+#pragma unroll
+        for (int t = 0; t < 8; t++) f[t] += r[t];
+        __builtin_amdgcn_sched_barrier(0);
+        return;
+    }
 #pragma unroll
     for (int nu = 0; nu < 4; nu++) {
         if (nu == MU || (nu == 0 && W.dn0) || (nu == 1 && W.dn1)) continue;
@@ -732,9 +773,9 @@ void stage_quad_kernel(StageArgs a) {
     const int mu = __builtin_amdgcn_readfirstlane(((threadIdx.x >> 6) + b) & 3);
 
     const int in = (c.cur + 3 * a.step + a.stage) & 1;
-    const Links<R, NE> G{as_global<R>((const void *)(in ? c.W[1] : c.W[0])), c.stride};
-    QuadLinks<R, NE> W{{G}, &s, i - tb, false, false, false, false};
-    const OwnLink<R> O{G(mu, i)};
+    QuadLinks<R, NE> W{Links<R, NE>{as_global<R>((const void *)(in ? c.W[1] : c.W[0])), c.stride},
+                       &s, i - tb, false, false, false, false};
+    OwnLink<R> O{W.gl(mu, i)};
     W.put(mu, O.U);
     const Geo g = make_geo_inv(c, i);
     W.dn0 = __all((unsigned)(i + g.dn(0) - tb) < (unsigned)nw);
@@ -763,6 +804,7 @@ void stage_quad_kernel(StageArgs a) {
     const double eps = a.step < c.n_full ? a.eps : c.eps_last;
     const R beps = (R)(kRkB[a.stage] * eps);
     const R ac = (R)kRkA[a.stage];
+    if constexpr (sizeof(R) == 8) O.U = W.own(mu);         // not held since the load (36 registers)
     update_link_z<R, NE>(O, as_global<R>(in ? c.W[0] : c.W[1]), as_global<R>(c.X), c.stride, mu, i,
                          raw_to_alg(f, -beps), ac, a.stage, reunit_now(a, c));
 }
@@ -999,7 +1041,7 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
         const int sel = buf_sel < 0 ? c.cur : ((c.cur + buf_sel) & 1);
-        const TwoRowLinks<R, NE> W{{as_global<R>((const void *)(sel ? c.W[1] : c.W[0])), c.stride}};
+        const Links<R, NE> W{as_global<R>((const void *)(sel ? c.W[1] : c.W[0])), c.stride};
         const Geo g = make_geo_inv(c, i);
         const int nw = min(kTile, c.V - tb);
         switch (pair) {
@@ -1039,7 +1081,7 @@ __global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict_
     __shared__ double part[2][2][kTile];
     double v[4] = {0, 0, 0, 0};
     if (i < c.V) {
-        const TwoRowLinks<R, NE> W{{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride}};
+        const Links<R, NE> W{as_global<R>((const void *)(c.cur ? c.W[1] : c.W[0])), c.stride};
         const Geo g = make_geo_inv(c, i);
         const int nw = min(kTile, c.V - tb);
         switch (pair) {

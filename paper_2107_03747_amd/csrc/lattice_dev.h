@@ -345,30 +345,6 @@ struct Links {
     }
 };
 
-// Links read as their rows 0 and 1, row 2 = conj(row0 x row1) formed in
-// registers.  Only FP64 differs from Links: a context's links are SU(3) (to
-// 1e-10 by the load's check, to rounding after any update), the FP64 kernels
-// that read neighbours are bound by the bytes that pass the L1 (a link read is
-// 9 KB per wave at 64 B per cycle), and their arithmetic units have room.  Two
-// thirds of the bytes: measurement of 2 x 16x16x48x48 590 -> 400 us, quad
-// stage on 10x10x30x30 x 40 2010 -> 1912 us, 8x8x24x24 x 96 1478 -> 1455 us.
-template <class R, int NE>
-struct TwoRowLinks : Links<R, NE> {
-    __device__ __forceinline__ M3<R> operator()(int mu, int i) const {
-        if constexpr (sizeof(R) == 8) {
-            gptr<const v2<R>> q = this->p + (size_t)(mu * NE) * this->stride;
-            const unsigned u = lane_off<R>(i);
-            M3<R> U;
-#pragma unroll
-            for (int e = 0; e < 6; e++) U.e[e / 3][e % 3] = ld(q + (size_t)e * this->stride, u);
-            rebuild_row2(U);
-            return U;
-        } else {
-            return Links<R, NE>::operator()(mu, i);
-        }
-    }
-};
-
 template <class R, int NE, bool PIN = false>
 __device__ __forceinline__ void store_link(gptr<v2<R>> p, int stride, int mu, int i,
                                            const M3<R> &U) {

@@ -9,9 +9,7 @@
 // The kernels are the ones of the context path (measure_dev.h) with a
 // canonical-layout link accessor; the partials have the same (tile, pair)
 // layout and are summed in the same order, so the result equals that of
-// tgf_measure on a TGF_F64_FULL context holding the same links to rounding
-// (the context, whose links were checked, reads rows 0 and 1 of a link and
-// forms row 2; these links are not checked and are read whole).
+// tgf_measure on a TGF_F64_FULL context holding the same links.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -345,6 +345,19 @@ __device__ __forceinline__ void r2_raw(const R2<R> &P, R k[8]) {
     k[7] = b[1].y - im22;
 }
 
+// Raw form of a matrix given by its three rows (no unitarity assumed).
+template <class R>
+__device__ __forceinline__ void m_raw(const M3<R> &M, R k[8]) {
+    k[0] = M.e[0][1].x - M.e[1][0].x;
+    k[1] = M.e[0][1].y + M.e[1][0].y;
+    k[2] = M.e[0][2].x - M.e[2][0].x;
+    k[3] = M.e[0][2].y + M.e[2][0].y;
+    k[4] = M.e[1][2].x - M.e[2][1].x;
+    k[5] = M.e[1][2].y + M.e[2][1].y;
+    k[6] = M.e[0][0].y - M.e[2][2].y;
+    k[7] = M.e[1][1].y - M.e[2][2].y;
+}
+
 // s * P_ah(M) in the 8-real su(3) form from the raw form of M.
 template <class R>
 __device__ __forceinline__ Alg<R> raw_to_alg(const R k[8], R s) {
