@@ -181,72 +181,20 @@ __device__ __forceinline__ void subgroup_update(M3<double> &U, M3<double> &Om, c
     rows_left_mul<RA, RB>(Om, A);
 }
 
-// Links of the staples, read as their rows 0 and 1: row 2 of an SU(3) matrix is
-// conj(row0 x row1), formed where a product needs it.  The kernel is bound by
-// the fetches of neighbour links that miss the L2 (half of its requests), so a
-// third of every link is not fetched; the two-row products and their third
-// rows take about as many operations as full products, and fewer registers
-// (223, two waves per SIMD; 346 and one with full links).  Launch on 2.0e6
-// sites (32 of 8x8x24x24, 8 of 6x6x18x18, 8 of 10x10x30x30): 514 -> 350 us on
-// average, 1.7 GB read past the L2 and 0.29 GB written, 5.7 TB/s.  Tried on
-// this form: staples fenced apart, no change; three or four waves per SIMD
-// (spills) +26% and +63%; one work-group per CU -4% on large batches.
-struct StapleLinks {
-    gptr<const v2<double>> p;
-    int stride;
-    __device__ __forceinline__ R2<double> operator()(int mu, int i) const {
-        gptr<const v2<double>> q = p + (size_t)(mu * 9) * stride;
-        const unsigned u = lane_here(lane_off<double>(i));
-        R2<double> U;
-#pragma unroll
-        for (int e = 0; e < 6; e++) U.e[e / 3][e % 3] = ld(sgpr_base(q + (size_t)e * stride), u);
-        return U;
-    }
-};
-
-// rows 0, 1 of A^+ B
-__device__ __forceinline__ R2<double> r2_mul_dn(const M3<double> &A, const M3<double> &B) {
-    R2<double> C;
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            cx<double> s = {0.0, 0.0};
-            s = cmadd_cn(s, A.e[0][i], B.e[0][j]);
-            s = cmadd_cn(s, A.e[1][i], B.e[1][j]);
-            s = cmadd_cn(s, A.e[2][i], B.e[2][j]);
-            C.e[i][j] = s;
-        }
-    return C;
-}
-
-// S += the upper staple U_nu(n+mu) [U_nu(n) U_mu(n+nu)]^+ times Z^*_{mu nu}(n)
-// and the lower one [U_mu(n-nu) U_nu(n+mu-nu)]^+ U_nu(n-nu) times
-// Z_{mu nu}(n-nu); both are SU(3) times a cube root of unity
-__device__ __forceinline__ void add_staples(M3<double> &S, const StapleLinks &W, const CfgDesc &c,
-                                            const Geo &g, int mu, int nu) {
-    const int k = twist_exp(c, mu, nu);
-    const int jmu = g.i + g.up(mu), jnu = g.i + g.up(nu);
-    R2<double> st = r2_mul_nd(W(nu, jmu), r2_full(r2_mul_nn(W(nu, g.i), r2_full(W(mu, jnu)))));
-    if (k && g.n(mu) == 0 && g.n(nu) == 0) r2_scale(st, cconj(omega_pow<double>(k)));
-    m_acc(S, r2_full(st));
-    const int j = g.i + g.dn(nu);
-    st = r2_mul_dn(r2_full(r2_mul_nn(W(mu, j), r2_full(W(nu, j + g.up(mu))))), r2_full(W(nu, j)));
-    if (k && g.n(mu) == 0 && g.back(nu) == 0) r2_scale(st, omega_pow<double>(k));
-    m_acc(S, r2_full(st));
-}
-
 template <int MU>
 __device__ __forceinline__ void mc_link(const McArgs &a, const CfgDesc &c, int i) {
     void *base = c.cur ? c.W[1] : c.W[0];
-    const StapleLinks W{as_global<double>((const void *)base), c.stride};
+    const Links<double, 9, true> W{as_global<double>((const void *)base), c.stride};
     const Geo g = make_geo(c, i);
     M3<double> S;
     m_zero(S);
 #pragma unroll
-    for (int nu = 0; nu < 4; nu++)
-        if (nu != MU) add_staples(S, W, c, g, MU, nu);
-    M3<double> U = Links<double, 9, true>{as_global<double>((const void *)base), c.stride}(MU, i);
+    for (int nu = 0; nu < 4; nu++) {
+        if (nu == MU) continue;
+        m_acc(S, upper_staple(W, c, g, MU, nu));
+        acc_lower_staple(S, W, c, g, MU, nu);
+    }
+    M3<double> U = W(MU, i);
     M3<double> Om = mul_nn(U, S);
     const uint32_t cfg = (uint32_t)c.user;
     subgroup_update<0, 1, 0>(U, Om, a, MU, i, cfg);
@@ -261,7 +209,7 @@ __device__ __forceinline__ void mc_link(const McArgs &a, const CfgDesc &c, int i
 // tile table counts V/2 sites per configuration; blocks are laid out
 // XCD-contiguously.
 template <int MU>
-__global__ __launch_bounds__(256, 2) void mc_kernel(McArgs a) {
+__global__ __launch_bounds__(256) void mc_kernel(McArgs a) {
     const int nb = (a.n_tiles + 3) >> 2;
     const int b = remap_block(blockIdx.x, nb, 1);
     if (b >= nb) return;
