@@ -422,7 +422,7 @@ __device__ __forceinline__ void stage_body(const SunStageArgs &a, const CfgDesc 
     expm1_neg<N>(z, m, e);
 #pragma unroll
     for (int mu = 0; mu < 4; mu++) {
-        const Zm n = mul<N, true>(a_of_nat<N>(e[mu]), u[mu], u[mu]);
+        const Zm n = zm_add(u[mu], mul<N, true>(a_of_nat<N>(e[mu]), u[mu], zero));
         if (mine) st_nt(Wout + (size_t)(mu * N * N) * st, off, cx<double>{n.r, n.i});
     }
 }
