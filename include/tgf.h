@@ -254,8 +254,9 @@ tgf_status tgf_unitarity(tgf_ctx *c, int32_t cfg, double *out);
  * The plaquette-sharing variants, whose rounding depends on the other
  * configurations of a work-group, are never chosen (tgf_set_variant still
  * selects them).  cache_path (may be NULL): a text file of "key value" lines
- * (one per variant choice and per class shape) read before and appended
- * after tuning.  Synchronises. */
+ * (one per variant choice, by the variant's name, and per class shape) read
+ * before and appended after tuning; an entry that names no variant of the
+ * library is timed anew.  Synchronises. */
 tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path);
 
 /* Sites per work-group of the LDS-staged variants for configuration cfg

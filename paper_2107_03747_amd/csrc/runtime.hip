@@ -14,6 +14,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <fstream>
 #include <new>
@@ -1063,12 +1064,23 @@ static std::string tune_key(tgf_ctx *c) {
     return k.str();
 }
 
-// Cache key of one extent class's work-group shape under a variant.
+// Cache key of one extent class's work-group shape under a variant (an SU(3)
+// index: that table is only ever appended to).
 static std::string block_key(tgf_ctx *c, int variant, const int d[4]) {
     std::ostringstream k;
     k << arch_name() << "/st" << (int)c->st << "/v" << variant << "/blk/" << d[0] << "x" << d[1]
       << "x" << d[2] << "x" << d[3];
     return k.str();
+}
+
+// The cache names a variant, it does not number it: an entry holds whatever
+// the tables of a later build look like, and an entry that names no variant of
+// this build (a number, as earlier builds wrote, too) is a miss.
+static std::string cache_name(tgf_ctx *c, int v) {
+    if (!c->general) return variant_name(v);
+    const int lds = sun_variant_lds(c->nc, v);
+    if (lds) return lds == 1 ? "lds" : "matrix";
+    return "rows" + std::to_string(sun_rows_per_lane(c->nc, v));
 }
 
 // A timed candidate replaces the incumbent only when faster by this fraction,
@@ -1082,19 +1094,19 @@ tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path) {
     for (int k = 0; k < c->n_cfg; k++)
         if (!c->L.cfg[k].loaded)
             return fail(TGF_E_STATE, "config " + std::to_string(k) + " not loaded");
-    std::vector<std::pair<std::string, int>> cache;
+    std::vector<std::pair<std::string, std::string>> cache;
     if (cache_path) {
         std::ifstream in(cache_path);
-        std::string k2;
-        int v;
-        while (in >> k2 >> v) cache.push_back({k2, v});
+        std::string k2, v2;
+        while (in >> k2 >> v2) cache.push_back({k2, v2});
     }
-    auto cached = [&](const std::string &key, int &out) {
+    // the last entry of a key that read() accepts
+    auto cached = [&](const std::string &key, auto read) {
         for (auto it = cache.rbegin(); it != cache.rend(); ++it)
-            if (it->first == key) { out = it->second; return true; }
+            if (it->first == key && read(it->second)) return true;
         return false;
     };
-    std::vector<std::pair<std::string, int>> found;
+    std::vector<std::pair<std::string, std::string>> found;
 
     // classes of configurations with equal extents (the work-group shape is tuned per class)
     std::vector<std::vector<int>> classes;
@@ -1155,7 +1167,12 @@ tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path) {
     for (int k = 0; k < c->n_cfg; k++) all[k] = k;
     const std::string vkey = tune_key(c);
     int best = -1;
-    if (!cached(vkey, best) || best < 0 || best >= c->variant_count()) {
+    auto read_variant = [&](const std::string &name) {
+        for (int v = 0; v < c->variant_count(); v++)
+            if (cache_name(c, v) == name) { best = v; return true; }
+        return false;
+    };
+    if (!cached(vkey, read_variant)) {
         std::vector<int> cand;
         if (c->general)
             for (int v = 0; v < c->variant_count(); v++) cand.push_back(v);
@@ -1167,7 +1184,7 @@ tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path) {
             if ((s = time_stage0(cand[j], all, ms))) return done(s);
             if (j == 0 || ms < best_ms * (1.0f - kTuneMargin)) { best = cand[j]; best_ms = ms; }
         }
-        found.push_back({vkey, best});
+        found.push_back({vkey, cache_name(c, best)});
     }
     c->variant = best;
 
@@ -1178,7 +1195,14 @@ tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path) {
             CfgHost &h0 = c->L.cfg[cl[0]];
             const std::string bkey = block_key(c, best, h0.d);
             int blk = 0;
-            if (!cached(bkey, blk) || blk < 1 || blk > kBlock) {
+            auto read_block = [&](const std::string &v) {
+                char *end = nullptr;
+                const long x = strtol(v.c_str(), &end, 10);
+                if (*end || x < 1 || x > kBlock) return false;
+                blk = (int)x;
+                return true;
+            };
+            if (!cached(bkey, read_block)) {
                 blk = default_block(h0.d);
                 const int alt = other_block(h0.d);
                 if (alt) {
@@ -1189,7 +1213,7 @@ tgf_status tgf_autotune(tgf_ctx *c, const char *cache_path) {
                     if ((s = time_stage0(best, cl, ms_alt))) return done(s);
                     if (ms_alt < ms_def * (1.0f - kTuneMargin)) blk = alt;
                 }
-                found.push_back({bkey, blk});
+                found.push_back({bkey, std::to_string(blk)});
             }
             for (int k : cl) c->L.cfg[k].blk = blk;
         }
