@@ -669,16 +669,16 @@ __device__ __forceinline__ void quad_plane(const QuadLinks<R, NE> &W, const CfgD
 
 // The term of this wave's own link at n + dir: r conjugated by U_dir(n), through
 // the plane's slot (which r takes afterwards; a wave's LDS accesses are carried
-// out in order) to the lane of that site.
+// out in order, and the fences keep the compiler to it) to the lane of that site.
 template <class R, int NE>
 __device__ __forceinline__ void quad_pass(const QuadLinks<R, NE> &W, const Geo &g, const R r[8],
                                           int dir, int slot, bool neg, R f[8]) {
     R t[8];
     conj_raw(W.own(dir), r, t);
     put_raw<R>(W.s->raw, slot, W.k, t);
-    __builtin_amdgcn_wave_barrier();
+    wave_fence();
     add_raw<R>(W.s->raw, slot, W.k + g.dn(dir), neg, f);
-    __builtin_amdgcn_wave_barrier();
+    wave_fence();
 }
 
 // The terms of the wave of direction MU: its planes -- wave 0 (0,1); 1 (2,3);

@@ -256,6 +256,15 @@ __host__ __device__ __forceinline__ int tile_order(int j, const CfgDesc &c) {
     return column_order(j, c, kTile, c.tchunk);
 }
 
+// Between a lane's LDS store and another lane's load within one wave: the
+// hardware carries out a wave's LDS accesses in order, this keeps the compiler
+// from moving one over the other (the barrier alone orders no memory access in
+// the compiler's eyes; that the addresses may alias did so far).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // A wave-uniform pointer taken through readfirstlane: the result is known to
 // be uniform (an SGPR pair) and opaque to re-association, so that
 // `sgpr_base(uniform) + lane offset` stays a global access with an SGPR base

@@ -45,10 +45,6 @@ struct CanonLinks {
     const v2<double> *p;
     v2<double> *buf;      // [64][9]
     int lane;
-    static __device__ __forceinline__ void fence() {
-        __builtin_amdgcn_wave_barrier();
-        asm volatile("" ::: "memory");
-    }
     __device__ __forceinline__ M3<double> operator()(int mu, int i) const {
         v2<double> t[9];
 #pragma unroll
@@ -57,17 +53,17 @@ struct CanonLinks {
             const int site = __shfl(i, s);
             t[k] = p[((size_t)site * 4 + mu) * 9 + (x - 9 * s)];
         }
-        fence();
+        wave_fence();
 #pragma unroll
         for (int k = 0; k < 9; k++) buf[64 * k + lane] = t[k];
-        fence();
+        wave_fence();
         M3<double> U;
 #pragma unroll
         for (int e = 0; e < 9; e++) {
             const v2<double> z = buf[9 * lane + e];
             U.e[e / 3][e % 3] = {z.x, z.y};
         }
-        fence();
+        wave_fence();
         return U;
     }
 };
