@@ -268,8 +268,10 @@ tgf_status tgf_get_block(tgf_ctx *c, int32_t cfg, int32_t *sites);
 tgf_status tgf_set_block(tgf_ctx *c, int32_t cfg, int32_t sites);
 
 /* Select a stage-kernel variant by index (0 .. tgf_variant_count()-1), or
- * -1 for the built-in default ("quad_xcd", one wave per direction and tile;
- * general SU(N) contexts: variant 0). */
+ * -1 for the built-in default ("quad_xcd", one wave per direction and tile, or
+ * for large boxes of some extents, by extents and storage alone, "site_lds_xcd";
+ * general SU(N) contexts: variant 0).  tgf_get_variant answers "quad_xcd" for a
+ * context whose configurations' defaults differ. */
 tgf_status tgf_set_variant(tgf_ctx *c, int32_t variant);
 int32_t tgf_get_variant(tgf_ctx *c);
 int32_t tgf_variant_count(void);

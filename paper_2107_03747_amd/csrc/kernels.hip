@@ -77,6 +77,8 @@ struct StageArgs {
     double eps;
     int reunit_every;   // FP64 reunitarisation every this many steps (0 = never)
     int xcd;        // 1: remap blocks so each XCD owns a contiguous tile range
+    int mixed;      // 1: the quad kernel leaves out the configurations with CfgDesc::lds
+                    // (the LDS-staged kernel's table has no others)
 };
 
 // Reunitarise at the end of this step of configuration c?  Steps are counted
@@ -763,6 +765,7 @@ void stage_quad_kernel(StageArgs a) {
     if (b >= a.n_tiles) return;                            // whole work-group
     const int ci = find_cfg(a.tile_start, a.n_act, b);
     const CfgDesc c = a.cfgs[ci];
+    if (a.mixed && c.lds) return;
     const int tb = tile_order(b - a.tile_start[ci], c) * kTile;
     const int nw = min(kTile, c.V - tb);
     const int lane = threadIdx.x & 63;
@@ -1458,10 +1461,15 @@ hipError_t launch_stage(int variant, Prec p, bool c12, hipStream_t s, const CfgD
                         int n_blocks, int step, int stage, double eps, int reunit_every) {
     if (n_tiles <= 0) return hipSuccess;
     StageArgs a{cfgs, tile_start, n_act, n_tiles, blk_start, n_blocks, step, stage, eps,
-                reunit_every, 0};
-    if (p == P_F64) return launch_stage_t<double, 9>(variant, s, a);
-    if (c12) return launch_stage_t<float, 6>(variant, s, a);
-    return launch_stage_t<float, 9>(variant, s, a);
+                reunit_every, 0, variant == V_MIXED ? 1 : 0};
+    auto launch = [&](int v) {
+        if (p == P_F64) return launch_stage_t<double, 9>(v, s, a);
+        if (c12) return launch_stage_t<float, 6>(v, s, a);
+        return launch_stage_t<float, 9>(v, s, a);
+    };
+    if (variant != V_MIXED) return launch(variant);
+    const hipError_t e = launch(V_QUAD_XCD);
+    return e != hipSuccess ? e : launch(V_SITE_LDS_XCD);
 }
 
 hipError_t launch_measure(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs,

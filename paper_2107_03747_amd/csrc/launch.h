@@ -30,8 +30,12 @@ enum Variant {
     V_SITE_PLQ_XCD = 11,
     V_QUAD = 12,      // a work-group per 64-site tile, one wave per direction, the
                       // site's loops dealt to the waves and shared through LDS
-    V_QUAD_XCD = 13,  // the default
-    V_COUNT = 14
+    V_QUAD_XCD = 13,
+    V_COUNT = 14,
+    // not selectable: the default of a context whose configurations differ in
+    // CfgDesc::lds, V_SITE_LDS_XCD for those that have it set and V_QUAD_XCD for
+    // the others, two launches
+    V_MIXED = V_COUNT
 };
 const char *variant_name(int v);
 

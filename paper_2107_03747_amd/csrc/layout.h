@@ -43,6 +43,7 @@ struct CfgDesc {
     int32_t blk;          // sites per work-group of the LDS-staged stage variants (<= 256)
     int32_t chunk;        // their launch order: 0 = site order, else columns of chunk blocks
     int32_t tchunk;       // the same for the quad variant's 64-site tiles
+    int32_t lds;          // 1: the default stage kernel is the LDS-staged one (lds_by_default)
     double eps_last;      // size of the short final step (0 if none)
     double t0;            // flow time at the start of this flow
     double inv[3];        // 1 / d[0..2] (make_geo_inv)

@@ -54,6 +54,7 @@ struct CfgHost {
     int stride;
     int tiles;
     int blk;                 // sites per LDS-staged work-group (default_block, or tuned)
+    bool lds;                // default stage kernel (lds_by_default)
     size_t offW[2], offX;
     int cur = 0;
     double t = 0;
@@ -125,6 +126,7 @@ Layout make_layout(int32_t n_cfg, const tgf_geom *g, tgf_storage st, int nc = 3,
         h.stride = (int)align_up((size_t)h.V, 256);
         h.tiles = (h.V + 63) / 64;
         h.blk = default_block(h.d);
+        h.lds = !general && lds_by_default(h.d, st == TGF_F64_FULL, st == TGF_F32_C12);
         tiles += h.tiles;
     }
     L.total_tiles = tiles;
@@ -207,10 +209,18 @@ struct tgf_ctx {
     int ne() const { return general ? nc * nc : (st == TGF_F32_C12 ? 6 : 9); }
     int x_entries() const { return general ? nc * nc : 4; }
     int variant_count() const { return general ? sun_variant_count(nc) : V_COUNT; }
+    // the variant in use; of a mixed default, the quad kernel
     int effective_variant() const {
-        if (general) return variant >= 0 ? variant : 0;
+        const int v = stage_variant();
+        return v == V_MIXED ? V_QUAD_XCD : v;
+    }
+    // the same as launch_stage takes it
+    int stage_variant() const {
         if (variant >= 0) return variant;
-        return V_QUAD_XCD;   // the fastest measured for all three storages
+        if (general) return 0;
+        int n = 0;
+        for (const CfgHost &h : L.cfg) n += h.lds;
+        return n == 0 ? V_QUAD_XCD : n == n_cfg ? V_SITE_LDS_XCD : V_MIXED;
     }
 };
 
@@ -240,6 +250,7 @@ void fill_desc(const tgf_ctx *c, const CfgHost &h, int user, CfgDesc &d) {
     d.blk = h.blk;
     d.chunk = block_chunk(h.d, h.blk);
     d.tchunk = tile_chunk(h.d);
+    d.lds = h.lds;
     d.W[0] = c->ws + h.offW[0];
     d.W[1] = c->ws + h.offW[1];
     d.X = c->ws + h.offX;
@@ -282,7 +293,7 @@ Plan make_plan(double t0, double t_end, double eps, double dt) {
 
 tgf_status run_launches(tgf_ctx *c, const std::vector<Launch> &ls, double eps, bool graph,
                         bool timing) {
-    const int variant = c->effective_variant();
+    const int variant = c->stage_variant();
     hipStream_t s = c->stream;
     auto issue = [&](const Launch &l) -> hipError_t {
         switch (l.kind) {
@@ -392,9 +403,13 @@ tgf_status run_check(tgf_ctx *c, int cfg, const void *src, double out[2]) {
 // half_sites: the tiles cover the V/2 sites of one parity (Monte Carlo).
 // reunit_every: the flow's reunitarisation period, for each configuration's
 // phase (steps done since its load, modulo the period).
+// lds_only: the work-group table of the LDS-staged kernel counts only the
+// configurations that run in it by default (V_MIXED), so that its launch order
+// spreads those over the XCDs.
 tgf_status upload_tables(tgf_ctx *c, const std::vector<int> &order, const std::vector<Plan> *plans,
                          std::vector<int> &tile_start, bool half_sites = false,
-                         int reunit_every = 0, std::vector<int> *blk_start = nullptr) {
+                         int reunit_every = 0, std::vector<int> *blk_start = nullptr,
+                         bool lds_only = false) {
     const int n = (int)order.size();
     tile_start.assign(n + 1, 0);
     std::vector<int> bs(n + 1, 0);
@@ -402,7 +417,7 @@ tgf_status upload_tables(tgf_ctx *c, const std::vector<int> &order, const std::v
         const CfgHost &h = c->L.cfg[order[k]];
         const int tiles = half_sites ? (h.V / 2 + 63) / 64 : h.tiles;
         tile_start[k + 1] = tile_start[k] + tiles;
-        bs[k + 1] = bs[k] + (h.V + h.blk - 1) / h.blk;
+        bs[k + 1] = bs[k] + (lds_only && !h.lds ? 0 : (h.V + h.blk - 1) / h.blk);
     }
     if (blk_start) *blk_start = bs;
     size_t bytes = sizeof(CfgDesc) * n + 2 * sizeof(int) * (n + 1);
@@ -764,7 +779,9 @@ tgf_status tgf_flow(tgf_ctx *c, const tgf_flow_params *p, tgf_obs *rows_host, in
     const bool fp32 = c->st != TGF_F64_FULL;
     const int reunit_every = fp32 ? p->reunit_every : 0;
     std::vector<int> ts, bs;
-    if ((s = upload_tables(c, order, &plans, ts, false, reunit_every, &bs))) return s;
+    if ((s = upload_tables(c, order, &plans, ts, false, reunit_every, &bs,
+                           !c->general && c->stage_variant() == V_MIXED)))
+        return s;
     // slot table
     if ((s = ensure_stage(c, sizeof(MeasSlot) * (size_t)std::max(n_events, 1) * n))) return s;
     MeasSlot *ms = (MeasSlot *)c->h_stage;

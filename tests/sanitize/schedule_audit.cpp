@@ -1,7 +1,8 @@
 // Host audit of the stage launches' shapes and orders (test infrastructure),
 // with the runtime's own rules (schedule.h): the column width that tile_chunk
 // gives a box divides its slice's tiles, and with it tile_order visits every
-// tile once; the same for the LDS-staged blocks (block_chunk, block_order).
+// tile once; the same for the LDS-staged blocks (block_chunk, block_order); the
+// default kernel's rule.
 #include <hip/hip_runtime.h>
 
 #include <array>
@@ -58,7 +59,29 @@ static void orders(std::array<int, 4> a) {
     }
 }
 
+// The default kernel is a rule of extents and storage; both answers on each
+// side of its lines.
+static void defaults() {
+    struct Want { std::array<int, 4> d; bool f64, f32, c12; };
+    for (const Want &w : std::vector<Want>{
+             {{8, 8, 24, 24}, false, false, false},     {{9, 9, 27, 27}, false, false, false},
+             {{9, 9, 54, 54}, false, false, false},     {{9, 9, 81, 81}, false, true, false},
+             {{9, 9, 162, 162}, false, true, true},     {{9, 9, 324, 324}, true, true, true},
+             {{8, 8, 384, 384}, false, false, false},   {{12, 12, 256, 256}, false, false, false},
+             {{16, 16, 48, 48}, false, false, false},   {{16, 16, 192, 192}, true, true, false},
+             {{32, 32, 96, 96}, true, true, false},     {{36, 36, 108, 108}, false, false, false},
+             {{64, 64, 48, 48}, false, false, false},   {{6, 6, 252, 252}, false, true, true},
+             {{2, 2, 8192, 8190}, false, false, false}}) {
+        checked += 3;
+        if (lds_by_default(w.d.data(), true, false) != w.f64 ||
+            lds_by_default(w.d.data(), false, false) != w.f32 ||
+            lds_by_default(w.d.data(), false, true) != w.c12)
+            fail("default kernel", w.d.data());
+    }
+}
+
 int main() {
+    defaults();
     for (int l = 2; l <= 40; l++) orders({l, l, 3 * l, 3});
     for (int l : {2, 3, 5, 8, 16, 20, 24, 31, 32, 64})
         for (int m : {2, 7, 16, 32, 48})
