@@ -186,44 +186,50 @@ __device__ __forceinline__ void measure_pair(const LK &W, const CfgDesc &c, cons
 }
 
 // Fixed-order sum of the (tile, pair) partials [t0, t1) of one configuration
-// (4 doubles each: e, q, plaquette, action) by a work-group of kSumThreads:
-// strided per-thread sums with four slots in flight, wavefront sums, then the
-// waves in a fixed order.  Valid in thread 0.  One work-group per
-// configuration is bound by the latency of its loads: with 256 threads and one
-// slot in flight the 442 thousand slots of 32x32x96x96 took 810 us.
+// (4 doubles each: e, q, plaquette, action) by a work-group of kSumThreads (the
+// first sum_threads of them): strided per-thread sums with four slots in
+// flight, wavefront sums, then the waves in a fixed order.  Valid in thread 0.
+// One work-group per configuration is bound by the latency of its loads: with
+// 256 threads and one slot in flight the 442 thousand slots of 32x32x96x96 took
+// 810 us, now 81.  Up to 1024 slots 256 threads load them all at once.
 constexpr int kSumThreads = 1024;
+__host__ __device__ __forceinline__ int sum_threads(int n) { return n <= 1024 ? 256 : kSumThreads; }
 __device__ __forceinline__ void sum_tile_partials(const double *__restrict__ partials, int t0,
                                                   int t1, double tot[4]) {
-    double acc[4][4] = {};
-    int t = t0 + (int)threadIdx.x;
-    for (; t + 3 * kSumThreads < t1; t += 4 * kSumThreads) {
+    const int nt = sum_threads(t1 - t0);
+    __shared__ double red[kSumThreads / 64][4];
+    if ((int)threadIdx.x < nt) {                       // whole waves
+        double acc[4][4] = {};
+        int t = t0 + (int)threadIdx.x;
+        for (; t + 3 * nt < t1; t += 4 * nt) {
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const double2 *p = (const double2 *)(partials + (size_t)(t + u * kSumThreads) * 4);
+            for (int u = 0; u < 4; u++) {
+                const double2 *p = (const double2 *)(partials + (size_t)(t + u * nt) * 4);
+                const double2 a = p[0], b = p[1];
+                acc[u][0] += a.x; acc[u][1] += a.y; acc[u][2] += b.x; acc[u][3] += b.y;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 3; u++, t += nt) {
+            if (t >= t1) continue;
+            const double2 *p = (const double2 *)(partials + (size_t)t * 4);
             const double2 a = p[0], b = p[1];
             acc[u][0] += a.x; acc[u][1] += a.y; acc[u][2] += b.x; acc[u][3] += b.y;
         }
-    }
-    for (; t < t1; t += kSumThreads) {
-        const double2 *p = (const double2 *)(partials + (size_t)t * 4);
-        const double2 a = p[0], b = p[1];
-        acc[0][0] += a.x; acc[0][1] += a.y; acc[0][2] += b.x; acc[0][3] += b.y;
-    }
-    constexpr int kW = kSumThreads / 64;
-    __shared__ double red[kW][4];
-    const int w = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const double v = wave_sum((acc[0][k] + acc[1][k]) + (acc[2][k] + acc[3][k]));
-        if ((threadIdx.x & 63) == 0) red[w][k] = v;
+        for (int k = 0; k < 4; k++) {
+            const double v = wave_sum((acc[0][k] + acc[1][k]) + (acc[2][k] + acc[3][k]));
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][k] = v;
+        }
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-        tot[k] = 0;
+    for (int k = 0; k < 4; k++) tot[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+    if (nt == 256) return;
 #pragma unroll
-        for (int x = 0; x < kW; x++) tot[k] += red[x][k];
-    }
+    for (int x = 4; x < kSumThreads / 64; x++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) tot[k] += red[x][k];
 }
 
 }  // namespace tgf

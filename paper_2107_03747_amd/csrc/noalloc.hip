@@ -68,19 +68,42 @@ struct CanonLinks {
     }
 };
 
+// The same links lane by lane: more cache lines per load, but no passage through
+// LDS between a link and its use.
+struct LaneLinks {
+    const v2<double> *p;
+    __device__ __forceinline__ M3<double> operator()(int mu, int i) const {
+        const v2<double> *s = p + ((size_t)i * 4 + mu) * 9;
+        M3<double> U;
+#pragma unroll
+        for (int e = 0; e < 9; e++) {
+            const v2<double> z = s[e];
+            U.e[e / 3][e % 3] = {z.x, z.y};
+        }
+        return U;
+    }
+};
+
 // One work-group per tile of 64 sites, one wave per dual plane pair; the
 // wave's FP64 sums go to partials[tile][pair][4] (as measure_kernel).  Lanes
 // past the last site repeat it and count nothing.  Each XCD takes a run of
 // tiles: 16x16x48x48 547 -> 503 us, 12x12x36x36 277 -> 195, 8x8x24x24 36 -> 34.
-__global__ __launch_bounds__(192, 2) void measure_canon_kernel(CfgDesc c, const double2 *links,
+// kStaged: CanonLinks at two waves per SIMD; else LaneLinks at one, for launches
+// that leave the SIMDs one wave anyway (kLaneTiles).  The sums are the same bit
+// for bit.
+template <bool kStaged>
+__global__ __launch_bounds__(192, kStaged ? 2 : 1) void measure_canon_kernel(CfgDesc c, const double2 *links,
                                                             double *partials) {
-    __shared__ v2<double> buf[3][64 * 9];
+    __shared__ v2<double> buf[kStaged ? 3 : 1][kStaged ? 64 * 9 : 1];
     const int tile = run_order(blockIdx.x, gridDim.x);
     const int pair = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int tb = tile * kTile;                               // site of lane 0
     const int nw = min(kTile, c.V - tb);
     double v[4] = {0, 0, 0, 0};
-    const CanonLinks W{(const v2<double> *)links, buf[pair], lane};
+    const auto W = [&] {
+        if constexpr (kStaged) return CanonLinks{(const v2<double> *)links, buf[pair], lane};
+        else return LaneLinks{(const v2<double> *)links};
+    }();
     const Geo g = make_geo_inv(c, tb + min(lane, nw - 1));
     switch (pair) {
         case 0: measure_pair<double, 0>(W, c, g, v, tb, nw); break;
@@ -94,6 +117,14 @@ __global__ __launch_bounds__(192, 2) void measure_canon_kernel(CfgDesc c, const 
         o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
     }
 }
+
+// Up to this many tiles a work-group has a CU to itself and the latency of its
+// links is what counts; above, the bytes that pass the L1.  The whole call, links
+// through LDS and lane by lane (us): 4x4x12x12 19.2 and 13.7, 6x6x18x18 (183
+// tiles) 24.8 and 19.0, 8x8x16x16 (256) 19.8 and 16.0, 6x6x24x24 (324) 32.3 and
+// 31.1, 8x8x24x24 (576) 35.3 and 34.0, 9x9x27x27 (923) 63 and 69, 10x10x30x30
+// 92 and 108.
+constexpr int kLaneTiles = 256;
 
 // One work-group: the fixed-order sum of the n_tiles x 3 partials, written as
 // one tgf_obs {t, E, t^2 E, plaq, Q, action} to out.
@@ -173,12 +204,12 @@ extern "C" tgf_status tgf_measure_noalloc(const tgf_geom *geom, const void *link
     c.V = (int)V;
     const int n_tiles = (int)((V + kTile - 1) / kTile);
     hipStream_t s = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(measure_canon_kernel, dim3(n_tiles), dim3(192), 0, s, c,
-                       (const double2 *)links_dev, part);
+    hipLaunchKernelGGL(n_tiles <= kLaneTiles ? measure_canon_kernel<false> : measure_canon_kernel<true>,
+                       dim3(n_tiles), dim3(192), 0, s, c, (const double2 *)links_dev, part);
     e = hipGetLastError();
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(finalize_canon_kernel, dim3(1), dim3(kSumThreads), 0, s, (int)V, n_tiles, t,
-                           (const double *)part, (double *)out_dev);
+        hipLaunchKernelGGL(finalize_canon_kernel, dim3(1), dim3(sum_threads(n_tiles * 3)), 0, s,
+                           (int)V, n_tiles, t, (const double *)part, (double *)out_dev);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return nfail(TGF_E_HIP, std::string("launch: ") + hipGetErrorString(e));
