@@ -99,11 +99,10 @@ __device__ __forceinline__ Herm<R> g_of_raw9(const R k[9]) {
 // with Z^*_{mu nu} of its base site; also returns Re Tr of leaf 1 (the
 // plaquette).  Leaves 2, 3 and 4 are plaquettes of the sites n - nu, n - mu
 // and n - mu - nu carried to n: leaf 2 = U_nu(n-nu)^+ P(n-nu) U_nu(n-nu), and
-// leaves 3 + 4 = U_mu(n-mu)^+ [leaf 1 + leaf 2](n-mu) U_mu(n-mu).  When lanes
-// hold consecutive sites (tb = site of lane 0, nw active lanes; tb < 0: they
-// do not) and every active lane finds site n - nu (n - mu) in the wave, the
-// leaf sum of that site is taken from its lane and conjugated; otherwise the
-// leaves are formed link by link.
+// leaves 3 + 4 = U_mu(n-mu)^+ [leaf 1 + leaf 2](n-mu) U_mu(n-mu).  Lanes hold
+// consecutive sites (tb = site of lane 0, nw sites).  Where every active lane
+// finds site n - nu (n - mu) in the wave, the leaf sum of that site is taken
+// from its lane and conjugated; otherwise the leaves are formed link by link.
 template <class R, class LK>
 __device__ __forceinline__ Herm<R> clover_G(const LK &W, const CfgDesc &c, const Geo &g, int mu,
                                             int nu, R &retr_plaq, int tb, int nw) {
@@ -123,7 +122,7 @@ __device__ __forceinline__ Herm<R> clover_G(const LK &W, const CfgDesc &c, const
     L = r2_mul_nd(L, W(nu, i));
     retr_plaq = leaf_raw9(L, k && g.n(mu) == 0 && g.n(nu) == 0, zs, s);
     // leaf 2: Z^*(n-nu) U_nu(n-nu)^+ U_mu(n-nu) U_nu(n-nu+mu) U_mu(n)^+
-    if (tb >= 0 && __all((unsigned)(i_n - tb) < (unsigned)nw)) {
+    if (__all((unsigned)(i_n - tb) < (unsigned)nw)) {
 #pragma unroll
         for (int x = 0; x < 9; x++) u[x] = __shfl(s[x], i_n - tb);
         conj_raw9(W(nu, i_n), u, t);
@@ -136,7 +135,7 @@ __device__ __forceinline__ Herm<R> clover_G(const LK &W, const CfgDesc &c, const
     }
 #pragma unroll
     for (int x = 0; x < 9; x++) s[x] += t[x];
-    if (tb >= 0 && __all((unsigned)(i_m - tb) < (unsigned)nw)) {
+    if (__all((unsigned)(i_m - tb) < (unsigned)nw)) {
         // leaves 3 + 4 from the leaf sum of site n - mu
 #pragma unroll
         for (int x = 0; x < 9; x++) u[x] = __shfl(s[x], i_m - tb);
@@ -171,7 +170,7 @@ __device__ __forceinline__ Herm<R> clover_G(const LK &W, const CfgDesc &c, const
 // over the wave into partials[tile][pair][4].
 template <class R, int PAIR, class LK>
 __device__ __forceinline__ void measure_pair(const LK &W, const CfgDesc &c, const Geo &g,
-                                             double out[4], int tb = -1, int nw = 0) {
+                                             double out[4], int tb, int nw) {
     constexpr int a0 = 0, a1 = PAIR + 1;                       // (0,1) (0,2) (0,3)
     constexpr int b0 = PAIR == 0 ? 2 : 1;
     constexpr int b1 = PAIR == 2 ? 2 : 3;                      // (2,3) (1,3) (1,2)

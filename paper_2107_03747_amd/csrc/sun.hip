@@ -879,20 +879,6 @@ __device__ __forceinline__ void lds_fence() {
 __device__ __forceinline__ void pin(cx<double> &z) {
     asm volatile("" : "+v"(z.x), "+v"(z.y)::"memory");
 }
-// entry r of a row for this lane's row index r, by selection; the empty asm
-// per step keeps the compiler from turning the selection into an indexed
-// load from a private copy of the row
-template <int N>
-__device__ __forceinline__ cx<double> own_entry(const Row<N> &a, int r) {
-    cx<double> v = a.e[0];
-#pragma unroll
-    for (int j = 1; j < N; j++) {
-        if (r == j) v = a.e[j];
-        asm volatile("" : "+v"(v.x), "+v"(v.y));
-    }
-    return v;
-}
-
 template <int N>
 __device__ __forceinline__ void pin_row(Row<N> &c) {
 #pragma unroll
