@@ -190,9 +190,21 @@ __device__ __forceinline__ void measure_pair(const LK &W, const CfgDesc &c, cons
 // flight, wavefront sums, then the waves in a fixed order.  Valid in thread 0.
 // One work-group per configuration is bound by the latency of its loads: with
 // 256 threads and one slot in flight the 442 thousand slots of 32x32x96x96 took
-// 810 us, now 81.  Up to 1024 slots 256 threads load them all at once.
+// 810 us, now 259.  Up to 1024 slots 256 threads load them all at once.
 constexpr int kSumThreads = 1024;
 __host__ __device__ __forceinline__ int sum_threads(int n) { return n <= 1024 ? 256 : kSumThreads; }
+// acc[u] += slots t + u NT for u = 0 .. 3, those below t1
+template <int NT>
+__device__ __forceinline__ void add_slots(const double *__restrict__ partials, int t, int t1,
+                                          double acc[4][4]) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        if (t + u * NT >= t1) continue;
+        const double2 *p = (const double2 *)(partials + (size_t)(t + u * NT) * 4);
+        const double2 a = p[0], b = p[1];
+        acc[u][0] += a.x; acc[u][1] += a.y; acc[u][2] += b.x; acc[u][3] += b.y;
+    }
+}
 __device__ __forceinline__ void sum_tile_partials(const double *__restrict__ partials, int t0,
                                                   int t1, double tot[4]) {
     const int nt = sum_threads(t1 - t0);
@@ -200,20 +212,18 @@ __device__ __forceinline__ void sum_tile_partials(const double *__restrict__ par
     if ((int)threadIdx.x < nt) {                       // whole waves
         double acc[4][4] = {};
         int t = t0 + (int)threadIdx.x;
-        for (; t + 3 * nt < t1; t += 4 * nt) {
+        if (nt == 256) {
+            add_slots<256>(partials, t, t1, acc);
+        } else {
+            for (; t + 3 * kSumThreads < t1; t += 4 * kSumThreads) {
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const double2 *p = (const double2 *)(partials + (size_t)(t + u * nt) * 4);
-                const double2 a = p[0], b = p[1];
-                acc[u][0] += a.x; acc[u][1] += a.y; acc[u][2] += b.x; acc[u][3] += b.y;
+                for (int u = 0; u < 4; u++) {
+                    const double2 *p = (const double2 *)(partials + (size_t)(t + u * kSumThreads) * 4);
+                    const double2 a = p[0], b = p[1];
+                    acc[u][0] += a.x; acc[u][1] += a.y; acc[u][2] += b.x; acc[u][3] += b.y;
+                }
             }
-        }
-#pragma unroll
-        for (int u = 0; u < 3; u++, t += nt) {
-            if (t >= t1) continue;
-            const double2 *p = (const double2 *)(partials + (size_t)t * 4);
-            const double2 a = p[0], b = p[1];
-            acc[u][0] += a.x; acc[u][1] += a.y; acc[u][2] += b.x; acc[u][3] += b.y;
+            add_slots<kSumThreads>(partials, t, t1, acc);
         }
 #pragma unroll
         for (int k = 0; k < 4; k++) {

@@ -88,11 +88,10 @@ struct LaneLinks {
 // wave's FP64 sums go to partials[tile][pair][4] (as measure_kernel).  Lanes
 // past the last site repeat it and count nothing.  Each XCD takes a run of
 // tiles: 16x16x48x48 547 -> 503 us, 12x12x36x36 277 -> 195, 8x8x24x24 36 -> 34.
-// kStaged: CanonLinks at two waves per SIMD; else LaneLinks at one, for launches
-// that leave the SIMDs one wave anyway (kLaneTiles).  The sums are the same bit
-// for bit.
+// kStaged: CanonLinks; else LaneLinks, for launches that leave a SIMD one wave
+// anyway (kLaneTiles).  The sums are the same bit for bit.
 template <bool kStaged>
-__global__ __launch_bounds__(192, kStaged ? 2 : 1) void measure_canon_kernel(CfgDesc c, const double2 *links,
+__global__ __launch_bounds__(192, 2) void measure_canon_kernel(CfgDesc c, const double2 *links,
                                                             double *partials) {
     __shared__ v2<double> buf[kStaged ? 3 : 1][kStaged ? 64 * 9 : 1];
     const int tile = run_order(blockIdx.x, gridDim.x);
