@@ -1023,7 +1023,8 @@ __global__ __launch_bounds__(256) void stage_link_kernel(StageArgs a) {
 // measurement: clover G (eq. gmunu), e(n), q(n), plaquette, action (measure_dev.h).
 // Each XCD takes a run of every configuration's tiles: 64, 16 and 16 boxes of
 // L = 8, 6, 10 in 12-real storage 750 -> 699 us, 24, 8 and 2 of L = 8, 6, 12 in
-// FP64 535 -> 503, against tiles dealt round.  (A run of the whole launch per
+// FP64 535 -> 503 (neighbours in two rows; whole, as now, 549), against tiles
+// dealt round.  (A run of the whole launch per
 // XCD: 922 us; the extents differ in cost, and events that measure some of the
 // configurations leave XCDs without work.)
 
@@ -1068,9 +1069,8 @@ __global__ __launch_bounds__(192) void measure_kernel(const CfgDesc *__restrict_
 // plane pair, leaves taken from the wave where it holds the neighbour; the
 // three pairs meet in LDS.  Each XCD takes a run of tiles (large boxes' in
 // columns), so that a tile finds its neighbours in its L2: FP64 16x16x48x48
-// 258 -> 244 us, 12x12x36x36 111 -> 94, FP32 16x16x48x48 140 -> 122.  (The
-// measurement above deals its tiles round: runs slowed the 96-box ensemble
-// by 14%, 810 -> 922 us, and gained nothing on one 16x16x48x48 box.)
+// 258 -> 244 us, 12x12x36x36 111 -> 94, FP32 16x16x48x48 140 -> 122 (FP64 with
+// neighbours read in two rows; whole, as now, 254).
 // to_x: q(n) goes to the configuration's accumulator
 // buffer, which a flow writes before it reads it, for the slice sums below.
 template <class R, int NE>
@@ -1110,7 +1110,7 @@ __global__ __launch_bounds__(192) void density_kernel(const CfgDesc *__restrict_
 // in increasing order.  FP64 partials, summed in a fixed order.  (One thread
 // per site forming all six clovers of its site link by link, lanes of a slice
 // not being neighbours, took 594 us on 16x16x48x48 FP64; the densities take
-// half of that and the sums 10.)
+// 254.)
 __global__ __launch_bounds__(256) void slice_sum_kernel(const CfgDesc *__restrict__ cfgs, int ci,
                                                         int dir, double *__restrict__ partials) {
     const CfgDesc &c = cfgs[ci];   // read in place (c.d is indexed at run time)

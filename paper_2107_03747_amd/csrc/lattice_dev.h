@@ -198,8 +198,8 @@ __host__ __device__ __forceinline__ int remap_block(int b, int nb, int xcd) {
 // per site in 12-real storage, L = 8: 0.17) ended last.  Stage launch of 64, 16
 // and 16 boxes of L = 8, 6, 10, runs -> chunks of 256 / 512 / 1024 / 2048
 // tiles: 12-real 803 -> 729 / 726 / 739 / 739 us, FP32 full 1060 -> 893 / 911 /
-// 929 / 931; of 24, 8 and 2 boxes of L = 8, 6, 12 in FP64: 664 -> 612 / 610 /
-// 628 / 664.  One extent gains nothing by
+// 929 / 931; in FP64, runs -> 512: 2252 -> 1892, and of 24, 8 and 2 boxes of
+// L = 8, 6, 12 726 -> 642.  One extent gains nothing by
 // runs: 96 boxes of L = 8 12-real 588 us dealt, 587 in runs, FP32 full 714 and
 // 702; 40 of L = 10 761 and 759, 972 and 986.
 constexpr int kDeal = 512;

@@ -81,7 +81,8 @@ hipError_t launch_check(Prec p, bool c12, hipStream_t s, const void *src, int V,
 
 // Topological charge per slice of direction `dir` for config ci (exec-order
 // descriptor at cfgs[ci]); partials need n_slices * ceil(slice_sites/256)
-// doubles, out n_slices doubles.
+// doubles, out n_slices doubles.  Overwrites the configuration's accumulator X
+// with the site densities (a flow writes X in its first stage before it reads it).
 hipError_t launch_slice_charge(Prec p, bool c12, hipStream_t s, const CfgDesc *cfgs, int ci,
                                int dir, int n_slices, int slice_sites, double *partials,
                                double *out);
@@ -102,14 +103,16 @@ hipError_t launch_mc(hipStream_t s, const CfgDesc *cfgs, const int *tile_start, 
 // max over ntiles pairs of defects in partials -> out[2]
 hipError_t launch_check_final(hipStream_t s, const double *partials, int ntiles, double *out);
 
-// General SU(N), FP64 full storage [mu][N^2][stride], 2 <= nc <= 8 (sun.hip).
+// General SU(N), FP64 full storage [mu][N^2][stride] (nc = 4, 7, 8:
+// [mu][stride][N^2]), 2 <= nc <= 8 (sun.hip, sun_mfma.hip).
 // Same tile table, ping-pong and partials conventions as the SU(3) launchers.
 // variant selects the rows held per lane (sun_rows_per_lane) and whether the
-// products exchange rows through cross-lane permutes or LDS (sun_variant_lds);
-// -1 = 0.
+// products exchange rows through cross-lane permutes or LDS, or run on the matrix
+// cores (sun_variant_lds); -1 = 0.
 int sun_variant_count(int nc);
 int sun_rows_per_lane(int nc, int variant);   // 0 if the variant does not exist
-int sun_variant_lds(int nc, int variant);     // 1 LDS operands, 0 permutes, -1 no such variant
+int sun_variant_lds(int nc, int variant);     // 2 matrix cores, 1 LDS operands, 0 permutes,
+                                              // -1 no such variant
 hipError_t launch_stage_sun(int nc, int variant, hipStream_t s, const CfgDesc *cfgs,
                             const int *tile_start, int n_act, int n_tiles, int step, int stage,
                             double eps);

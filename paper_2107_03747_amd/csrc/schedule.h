@@ -45,10 +45,10 @@ inline int block_chunk(const int d[4], int blk) {
 // while an n3 slice spans at most kTileSlice tiles (about what an XCD runs at a
 // time), else four (n0, n1) planes, or the largest divisor of the slice's tile
 // count below that.  Stage launch, site order against columns of 2 / 4 / 8
-// planes (us, 12-real, FP32 full, FP64): 32x32x96x96 1982, 2891, 6669 against
-// 1913, 2695, 6434 / 1850, 2626, 6331 / 1867, 2656, 6298; 16x16x48x48 x 6 (192
-// tiles per slice) 700, 892, 1775 against, for 4 / 8 / 16 planes, 687, 843,
-// 1668 / 690, 849, 1687 / 697, 873, 1734.
+// planes (us, 12-real and FP32 full): 32x32x96x96 1982, 2891 against 1913, 2695 /
+// 1850, 2626 / 1867, 2656; 16x16x48x48 x 6 (192 tiles per slice) 700, 892
+// against, for 4 / 8 / 16 planes, 687, 843 / 690, 849 / 697, 873.  FP64, site
+// order and four planes: 6864 and 6546, 1815 and 1717.
 constexpr int kTileSlice = 128;
 inline int tile_chunk(const int d[4]) {
     const long long s = (long long)d[0] * d[1] * d[2];

@@ -9,7 +9,8 @@
 // with Luscher's RK3 scheme in the same low-storage form as the SU(3) path,
 // X_i = B_i eps F + A_i X_{i-1}, W_{i+1} = exp(X_i) W_i.
 //
-// Work decomposition ("R rows per lane"): the N x N matrix of a link is spread
+// Work decomposition ("R rows per lane"; N = 4, 7 and 8 default to the matrix
+// cores, sun_mfma.hip): the N x N matrix of a link is spread
 // over L = N / R consecutive lanes of a wavefront, lane l holding rows
 // l R .. l R + R - 1, so a wave holds G = floor(64 / L) links.  In a product
 // C = A B every lane forms its own rows of C: its rows of A are local, the
@@ -19,9 +20,11 @@
 // way).  R = N is one thread per link with no permutes; R = 1 keeps the
 // fewest registers.  The choice is per context (the SU(N) variants).
 //
-// Storage: FP64, [mu][entry][site] with entry = r N + j, the structure of
-// arrays of the SU(3) full storage; the RK accumulator X is a full N x N
-// matrix per link in the same layout.  A work-group is one tile of 64 sites.
+// Storage: FP64, entry = r N + j, [mu][entry][site] (the structure of arrays of
+// the SU(3) full storage) or, for N = 4, 7 and 8, [mu][site][entry] (sun_aos); the
+// RK accumulator X is a full N x N matrix per link in the same layout.  A
+// work-group of the stage is one group of G sites, one wave per direction
+// (SiteGroups); of the measurement, a part of a 64-site tile (MeasShape, LdsMeas).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -327,21 +330,6 @@ __device__ __forceinline__ Blk<N, R> proj_ah_blk(const Blk<N, R> &m, const Grp &
     return a;
 }
 
-// exp(X) - 1 for X anti-Hermitian and traceless (the identity is left out, so
-// that the caller forms exp(X) U as U + (exp(X) - 1) U).  The exponential is
-// the part of a stage that a better formula shortens, the staples are fixed:
-//   N = 2   X^2 = -theta^2 1: exp(X) - 1 = (cos theta - 1) 1 + (sin theta / theta) X,
-//           no product at all;
-//   N = 3   Cayley-Hamilton, X^3 = p X + d 1: one product (X^2), then a series
-//           of three coefficients;
-//   N >= 4  a Taylor polynomial of degree 3 q + 2 in the grouping of Paterson
-//           and Stockmeyer, B_0 + Y^3 (B_1 + Y^3 (B_2 + ...)) with
-//           B_j = sum_{i<3} Y^(3j+i) / (3j+i)!: q + 2 products.
-// q is the least whose remainder theta^(3q+3) / (3q+3)! is below 2.8e-17
-// (theta = ||X||_F; a flow step of eps = 0.01 has theta of 0.01 to 0.06, q = 2,
-// four products where Horner's rule at degree 12 took eleven); above theta =
-// 1.4 the argument is halved s times and the result squared.  Each link's own
-// norm decides, so a link's result does not depend on its neighbours in a wave.
 // cos(theta) - 1 and sin(theta) / theta from t2 = theta^2: the series for
 // theta <= 1/2 (remainder 0.5^18 / 18! < 1e-21), the double-angle formulas above
 __device__ __forceinline__ void cosm1_sinc(double t2, double &cm, double &sn) {
@@ -445,6 +433,21 @@ __device__ __forceinline__ double im_dot(const Blk<N, R> &a, const Blk<N, R> &b,
     return group_sum<N, R>(s, g);
 }
 
+// exp(X) - 1 for X anti-Hermitian and traceless (the identity is left out, so
+// that the caller forms exp(X) U as U + (exp(X) - 1) U).  The exponential is
+// the part of a stage that a better formula shortens, the staples are fixed:
+//   N = 2   X^2 = -theta^2 1: exp(X) - 1 = (cos theta - 1) 1 + (sin theta / theta) X,
+//           no product at all;
+//   N = 3   Cayley-Hamilton, X^3 = p X + d 1: one product (X^2), then a series
+//           of three coefficients;
+//   N >= 4  a Taylor polynomial of degree 3 q + 2 in the grouping of Paterson
+//           and Stockmeyer, B_0 + Y^3 (B_1 + Y^3 (B_2 + ...)) with
+//           B_j = sum_{i<3} Y^(3j+i) / (3j+i)!: q + 2 products.
+// q is the least whose remainder theta^(3q+3) / (3q+3)! is below 2.8e-17
+// (theta = ||X||_F; a flow step of eps = 0.01 has theta of 0.01 to 0.06, q = 2,
+// four products where Horner's rule at degree 12 took eleven); above theta =
+// 1.4 the argument is halved s times and the result squared.  Each link's own
+// norm decides, so a link's result does not depend on its neighbours in a wave.
 template <int N, int R>
 __device__ __forceinline__ Blk<N, R> expm1_blk(Blk<N, R> x, const Grp &g) {
     const double n2 = re_dot<N, R>(x, x, g);

@@ -29,15 +29,17 @@
 // operand is read once per product.  A wave works on the four links of its
 // sites, so an upper plaquette serves both of its links: 46 products of
 // staples and 20 of the exponential and update per site and stage, against 52
-// and 48 (24 with this polynomial).
+// and 48 (20 with this polynomial).
 //
 // Stage launch, MI355X, against the rows-in-lanes kernels before: SU(4)
-// 4x4x16x16 x 48 (197k sites) 387 -> 235 us; SU(7) 4x4x28x28 x 6 1160 ->
-// 598 us; SU(8) 4x4x32x32 x 4 (131k sites) 1296 -> 499 us, which is the matrix
-// instructions' own time (66 products x 8 instructions x 16 cycles per site,
-// 0.45 ms at 2.4 GHz).  SU(4) is held by issue: 264 matrix and about 600 other
-// vector instructions per wave of four sites (680 MB per launch, no refetch).
-// Measurement of the same boxes: 433 -> 345, 1080 -> 672, 1500 -> 660 us.
+// 4x4x16x16 x 48 (197k sites) 386 -> 228 us; SU(7) 4x4x28x28 x 6 (75k) 1097 ->
+// 596 us; SU(8) 4x4x32x32 x 4 (66k) 1198 -> 481 us.  The matrix instructions'
+// own time is 0.225 ms of the last (66 products x 8 instructions x 16 cycles per
+// site on 1024 SIMDs at 2.4 GHz): the rest is waiting for operands, an adjoint
+// being read as two overlapping blocks.  SU(4) is held by issue: 264 matrix and
+// about 600 other vector instructions per wave of four sites (680 MB per launch,
+// no refetch; 85 us of matrix time).  Measurement of the same boxes: 433 -> 291,
+// 1098 -> 630, 1463 -> 672 us.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
