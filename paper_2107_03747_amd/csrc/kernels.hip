@@ -526,8 +526,10 @@ void stage_site_lds_kernel(StageArgs a) {
 // Stage launch, 3.5e6 sites of 8x8x24x24, 10x10x30x30, 16x16x48x48 in turn:
 // 12-real 613 -> 590, 824 -> 770, 709 -> 700 us (12x12x36x36 1020 -> 800);
 // FP32 full 865 -> 700, 1020 -> 1005, 980 -> 900; FP64 2110 -> 1504, 2440 ->
-// 2016, 2795 -> 1719.  Under this load the clock falls to 1.4-1.6 GHz, so what
-// is left is energy: operations and bytes moved, not waves or latency.  Tried:
+// 2016, 2795 -> 1719.  Under the 12-real ensemble's flow the clock falls
+// to 1.75 GHz of 2.4 (2.1 in the LDS-staged kernel) and a SIMD takes 3.1 cycles
+// per VALU instruction where two waves that issue together need two: energy
+// first, operations and bytes moved, then waiting.  Tried:
 // third rows of 12-real links kept in LDS (-6% instructions, 33 KB) +7%; six
 // waves per SIMD (own link re-read from LDS) +2%; links requested two or three
 // uses ahead +2% and +12% (registers).
